@@ -65,37 +65,29 @@ struct Batch {
 
 // Tile configuration of one grouped SGEMM launch, its requests sorted by
 // size from the largest down (every configuration gives the same bits, so
-// the choice is about speed alone).
-//  * One size: the table's configuration of that size.
-//  * Mixed sizes: 64x128x16 tiles with row-major B, a two-deep fetch and
-//    registers held to four waves per SIMD (configuration 29), the smallest
-//    tiles that still run near full rate.  The same tile at three waves per
-//    SIMD (17) ran the 32-rank uneven launch 3.5 % slower (671-674 against
-//    647-650 us), its pipelined sibling (25) slower again.  Small tiles
-//    balance the short and the long tiles of a mix over the CUs, where
-//    128x128 or larger tiles leave CUs idle at the end.
-// Tuning override for mixed sizes: GVM_SGEMM_MIX_CONFIG=<index>.
-constexpr int kMixConfig = 29;
+// the choice is about speed alone).  A mix of sizes that gives kMixConfig's
+// tiles (64x64, k-tiles of 64) two rounds over the chip takes it: small
+// tiles balance the short and the long requests over the CUs (the 32-rank
+// uneven launch: 477.5 us, against 478-482 us with 128x64 and 64x128 tiles
+// and more than 492 us with 128x128).  Everything else is chosen by
+// gemm_config_for.  Tuning override for mixed sizes:
+// GVM_SGEMM_MIX_CONFIG=<index>.
+constexpr int kMixConfig = 10;
 
-int gemm_group_config(const std::vector<Job*>& v) {
-  if (v.front()->req.n == v.back()->req.n) return gemm_config_for(v.front()->req.n);
+int gemm_group_config(const GemmGroup& g) {
+  const GemmConfig& mix = gemm_config(kMixConfig);
+  uint64_t tiles = 0;
+  for (uint32_t i = 0; i < g.count; ++i) {
+    const uint64_t n = g.d[i].n;
+    tiles += ((n + mix.bm - 1) / mix.bm) * ((n + mix.bn - 1) / mix.bn);
+  }
+  if (g.d[0].n == g.d[g.count - 1].n) return gemm_config_for(g);
   static const int env = [] {
     const char* e = getenv("GVM_SGEMM_MIX_CONFIG");
     return e ? atoi(e) : -1;
   }();
-  return env >= 0 && env < gemm_config_count() ? env : kMixConfig;
-}
-
-// Grid cap of an SGEMM launch over mixed sizes: one workgroup per tile, so
-// that the dispatcher hands the next tile to whichever CU frees up first
-// (tiles of different sizes differ in k-length by up to 5x; a persistent
-// grid deals them out statically).  GVM_SGEMM_MIX_GRID overrides.
-int gemm_mix_grid() {
-  static const int env = [] {
-    const char* e = getenv("GVM_SGEMM_MIX_GRID");
-    return e ? atoi(e) : 0;
-  }();
-  return env > 0 ? env : (1 << 24);
+  if (env >= 0 && env < gemm_config_count()) return env;
+  return tiles >= 2 * kPartitionCus ? kMixConfig : gemm_config_for(g);
 }
 
 // Order of a grouped batch's launches: 0 = dealt over both compute streams,
@@ -779,10 +771,9 @@ class HipDevice final : public Device {
         gg.d[i].C = reinterpret_cast<float*>(v[i]->slot + slot_out_offset(v[i]->lay));
         gg.d[i].n = static_cast<uint32_t>(n);
       }
-      const int cfgi = gemm_group_config(v);
+      const int cfgi = gemm_group_config(gg);
       finalize_gemm_group(gg, cfgi);
-      const bool mixed = v.front()->req.n != v.back()->req.n;
-      if ((e = mark()) == hipSuccess) e = launch_sgemm_group(gg, cfgi, s, mixed ? gemm_mix_grid() : 0);
+      if ((e = mark()) == hipSuccess) e = launch_sgemm_group(gg, cfgi, s);
     } else if (k == GVM_K_EP) {
       EpGroup eg{};
       eg.count = static_cast<uint32_t>(cnt);
@@ -957,7 +948,7 @@ class HipDevice final : public Device {
       const uint64_t f[7] = {static_cast<uint64_t>(j->rank), j->req.kernel_id, j->req.n,
                              static_cast<uint64_t>(j->copy_in) | (static_cast<uint64_t>(j->copy_out) << 1),
                              reinterpret_cast<uint64_t>(j->slot), reinterpret_cast<uint64_t>(j->pin),
-                             static_cast<uint64_t>(gemm_config_for(j->req.n))};
+                             static_cast<uint64_t>(gemm_config_forced())};
       key.append(reinterpret_cast<const char*>(f), sizeof(f));
     }
     return key;

@@ -1,0 +1,84 @@
+// Host-side choice of the SGEMM tile configuration of a launch (no HIP types;
+// a CPU test checks it).
+#pragma once
+
+#include <algorithm>
+#include <cstdint>
+
+namespace gvm {
+
+// Time of a launch under one tile configuration, in us:
+//
+//   t0 + W / peak * (k / x) * e_k,   x = tiles / 256,  k = ceil(x)
+//
+// with W the FLOP of the whole tiles (ragged edges padded to the tile, as the
+// kernel computes them), 157.3 TFLOP/s the chip's FP32 matrix rate, x the
+// tiles per CU and k / x what the fullest CU has more than the mean.  t0 is
+// the part no tile size takes away (launch, first fetch, store of C); e1, e2
+// and e3 are the inverse of the rate a CU reaches with one, two and more tiles
+// (one tile alone has nothing to hide its barriers and fetches behind).  t0
+// and e1 .. e3 are fitted to launches of 1, 2, 3, 4, 8 and 16 requests of 46
+// sizes from 64 to 2048 on an MI355X (rms 2-6 % per configuration).  Over
+// those 276 launches the cheapest configuration by this formula is on average
+// 0.5 % and at most 6.5 % slower than the fastest of all 30 measured, where
+// a table by size alone (tuned on 8 requests) is 13 % and up to 87 % slower
+// for 4 requests and 1.4 % and up to 10 % for 16.
+struct GemmCost {
+  int config;
+  uint32_t bm, bn;
+  float t0, e1, e2, e3;
+};
+constexpr GemmCost kGemmCosts[] = {
+    {0, 32, 32, 4.4f, 0.43f, 1.19f, 1.42f},    {1, 32, 32, 4.2f, 0.95f, 1.19f, 1.37f},
+    {3, 32, 64, 4.3f, 1.03f, 1.18f, 1.22f},    {5, 64, 32, 4.5f, 0.89f, 1.14f, 1.19f},
+    {6, 64, 64, 4.1f, 1.06f, 1.16f, 1.15f},    {9, 64, 64, 4.1f, 1.12f, 1.17f, 1.15f},
+    {10, 64, 64, 5.2f, 1.01f, 1.13f, 1.14f},   {11, 64, 96, 4.2f, 1.15f, 1.21f, 1.20f},
+    {13, 96, 96, 4.7f, 1.19f, 1.22f, 1.20f},   {17, 64, 128, 4.7f, 1.09f, 1.12f, 1.11f},
+    {18, 128, 64, 4.3f, 1.11f, 1.11f, 1.10f},  {22, 128, 128, 4.7f, 1.08f, 1.09f, 1.10f},
+    {24, 128, 256, 5.9f, 1.06f, 1.07f, 1.08f},
+};
+constexpr double kGemmPeakFlopPerUs = 157.3e6;
+constexpr double kGemmCus = 256.0;
+
+inline uint64_t gemm_tiles(const GemmCost& c, uint64_t n) {
+  return ((n + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn);
+}
+
+// Mixed sizes: the tiles differ in length by their n, so a CU may end on a
+// long one; its share of that (half, as measured on the 32-rank uneven mix)
+// is added to the mean time, or the mean to the longest tile where that is
+// the longer of the two.
+inline double gemm_launch_us(const GemmCost& c, uint32_t count, const uint32_t* n) {
+  double flop = 0.0, tiles = 0.0;
+  uint32_t nmax = 0, nmin = ~0u;
+  for (uint32_t i = 0; i < count; ++i) {
+    const double t = static_cast<double>(gemm_tiles(c, n[i]));
+    tiles += t;
+    flop += t * 2.0 * c.bm * c.bn * n[i];
+    nmax = std::max(nmax, n[i]);
+    nmin = std::min(nmin, n[i]);
+  }
+  const double x = tiles / kGemmCus;
+  const double k = static_cast<double>(static_cast<uint64_t>(x) + (x > static_cast<uint64_t>(x) ? 1 : 0));
+  const double e = k <= 1 ? c.e1 : k <= 2 ? c.e2 : c.e3;
+  const double mean = flop / kGemmPeakFlopPerUs * e;
+  if (nmin == nmax) return c.t0 + mean * k / x;
+  const double longest = 2.0 * c.bm * c.bn * nmax * kGemmCus / kGemmPeakFlopPerUs * e;
+  return c.t0 + std::max(mean, longest) + 0.5 * std::min(mean, longest);
+}
+
+// The cheapest configuration for one launch of requests of sizes n[0..count).
+inline int gemm_cheapest(uint32_t count, const uint32_t* n) {
+  int best = kGemmCosts[0].config;
+  double t_best = 0.0;
+  for (const GemmCost& c : kGemmCosts) {
+    const double t = gemm_launch_us(c, count, n);
+    if (&c == &kGemmCosts[0] || t < t_best) {
+      t_best = t;
+      best = c.config;
+    }
+  }
+  return best;
+}
+
+}  // namespace gvm

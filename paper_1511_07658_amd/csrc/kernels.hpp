@@ -90,20 +90,25 @@ struct EpGroup {
   EpDesc d[kMaxGroup];
 };
 
-// SGEMM tile configurations available to the tuner.  A configuration is a
-// pure function of n (see gemm_config_for), so a request always runs with the
-// same tiles whatever it is grouped with.
+// SGEMM tile configurations available to the tuner.  Every configuration sums
+// a C element in the same order, so the choice changes a launch's time and
+// never its bits.
 struct GemmConfig {
   int id;
   int bm, bn, bk;   // macro tile of one workgroup
   int wm, wn;       // waves along M and N (wave tile = bm/wm x bn/wn)
-  bool bt;          // B staged k-contiguous in LDS (transposed), else row-major
+  bool bt;          // B staged k-contiguous in LDS (transposed), else row-major (every one now)
 };
 
 int gemm_config_count();
 const GemmConfig& gemm_config(int idx);
-// Tile configuration used for size n (table written by the tuner, compiled in).
-int gemm_config_for(uint64_t n);
+// Tile configuration of one launch of the sizes n[0 .. count), or of a group
+// whose sizes are filled in.
+int gemm_config_for(uint32_t count, const uint32_t* n);
+int gemm_config_for(const GemmGroup& g);
+// The configuration forced for every launch (by gemm_config_force or the
+// environment), or -1.
+int gemm_config_forced();
 // Override the table (tuner only): config index for every n, or -1 to restore.
 void gemm_config_force(int idx);
 
@@ -116,10 +121,9 @@ constexpr uint64_t kBsUnit = 4096;    // options per Black-Scholes work unit (th
 hipError_t launch_vecadd_group(const VecGroup& g, hipStream_t s, int grid_cap = 0);
 hipError_t launch_vecmul_group(const VecGroup& g, hipStream_t s, int grid_cap = 0);
 hipError_t launch_bs_group(const BsGroup& g, hipStream_t s, int grid_cap = 0);
-// grid_cap >= total_units asks for one workgroup per tile; for a group of
-// mixed sizes the tiles are then spread over the XCDs by their k-steps
-// (GemmGroup.xcd_begin) instead of by count.
-hipError_t launch_sgemm_group(const GemmGroup& g, int config_idx, hipStream_t s, int grid_cap = 0);
+// One workgroup per tile; for a group of mixed sizes the tiles are spread over
+// the XCDs by their k-steps (GemmGroup.cut) instead of by count.
+hipError_t launch_sgemm_group(const GemmGroup& g, int config_idx, hipStream_t s);
 // EP-like tally: one launch over the work units of every request (partials),
 // then one workgroup per request sums its partials.
 hipError_t launch_ep_group(const EpGroup& g, hipStream_t s, int grid_cap = 0);

@@ -102,7 +102,7 @@ extern "C" int gvm_plain_run_noalloc(int kernel_id, const void* d_in, void* d_ou
     gvm::GemmGroup g{};
     g.count = 1;
     g.d[0] = gvm::GemmDesc{fin, fin + n * n, fout, static_cast<uint32_t>(n), 0, 0, 0};
-    const int c = gvm::gemm_config_for(n);
+    const int c = gvm::gemm_config_for(g);
     gvm::finalize_gemm_group(g, c);
     e = gvm::launch_sgemm_group(g, c, s);
   }

@@ -1,11 +1,11 @@
 // SGEMM C = A B (Table 3 "MM", single precision) for the GVM on gfx950:
-// FP32 MFMA (v_mfma_f32_32x32x2_f32) on LDS-staged, double-buffered tiles,
-// as one grouped persistent launch over the tiles of every request of the
-// group.  The unit -> request map is a search over the per-request first tile
-// held in the kernel arguments; a tile is always computed by the same code in
-// the same order, whatever else is in the group, so a rank's C is
-// bit-identical alone and in the mix.
+// FP32 MFMA on LDS-staged, double-buffered tiles, as one grouped launch over
+// the tiles of every request of the group, one workgroup per tile.  The tile
+// -> request map is a search over the per-request first tile held in the
+// kernel arguments; every tile configuration sums a C element in the same
+// order, so a rank's C is bit-identical alone and in any mix.
 #include "gemm_balance.hpp"
+#include "gemm_choice.hpp"
 #include "group_device.hpp"
 
 #include <algorithm>
@@ -17,99 +17,147 @@ namespace gvm {
 namespace {
 
 // ---------------------------------------------------------------- SGEMM
-//
-// Workgroup tile BM x BN, k-step BK, WM x WN waves; each wave owns a
-// (BM/WM) x (BN/WN) block of C as (BM/WM/32) x (BN/WN/32) accumulators of
-// one 32x32 MFMA each.  v_mfma_f32_32x32x2_f32 multiplies a 32x2 slice of A
-// by a 2x32 slice of B; lane l supplies A[l%32][k(l)] and B[k(l)][l%32] and
-// lane group g = l/32 selects which of the two k values it carries.  Each
-// run of eight k (8m .. 8m + 7) feeds four MFMA steps, with the k pairs
-// (8m + t, 8m + 4 + t) for t = 0 .. 3, g = 0 the smaller k: every C element
-// sums the pairs (0, 4), (1, 5), (2, 6), (3, 7), (8, 12), ... in that order
-// into one accumulator whatever the tile configuration, so all
-// configurations give the same bits and requests of any sizes may share one
-// launch.
-//
-// In LDS the k index of a tile is stored permuted, so that the KH = BK/2
-// values a lane multiplies in the KH steps of a tile sit side by side: k =
-// 8m + 4h + t (h in {0, 1}, t in 0 .. 3) goes to k' = h * KH + 4m + t.  A
-// run of four k stays contiguous, so a fetched float4 is still one 16-byte
-// LDS write, to the same banks as without the permutation.  A sits as
-// As[m][k'] (rows padded by 4 floats), and a lane's A fragments of a whole
-// tile are read with 16-byte LDS reads.  B has two stagings, chosen per tile
-// configuration by the tuner:
-//  * BT: Bs[n][k'], B transposed on the way in (each thread fetches four
-//    k-rows of one column, coalesced along n); B fragments are then 16-byte
-//    reads like A's;
-//  * row-major: Bs[k'][n] from float4 loads along n (k-row k goes to row
-//    k'); B fragments are 4-byte reads (one per MFMA step and column block),
-//    the two lane groups on rows BK/2 apart.
-// All fragments of a k-step are read before its MFMAs.  Double buffering:
-// the next tile is fetched into registers at the start of a k-step and
-// written to the other LDS buffer half-way through the MFMAs, so one barrier
-// per k-step remains.  Interior tiles take unchecked loads and stores; edge
-// tiles check every element and read zeros outside the matrix.
-//
-// PIPE variant: the fragments of the next k-tile are read from LDS into a
-// second register set while the MFMAs of the current one run, so no k-step
-// starts by waiting for LDS.  Tile t is written to LDS buffer t % 2 during
-// step t - 2, its fragments read during step t - 1 and multiplied in step t;
-// one barrier at the end of each step orders both hazards (a write of tile
-// t + 2 follows every read of tile t, which shares its buffer; a read of
-// tile t + 1 follows every write of it).  Tile 0's fragments are read in the
-// prologue, so a barrier follows them before step 0 writes tile 2.  The k
-// order of every C element is the same as without PIPE.
-//
-// Persistent grid, XCD-aware: the units (tiles, requests in order, tiles of a
-// request row-major) are dealt to the 8 XCDs in contiguous blocks, so that
-// tiles sharing rows of A and columns of B share an L2.
-//
-// Balanced grid (mixed sizes, one workgroup per tile): the blocks are cut by
-// work instead of by count.  The requests come largest first, so equal
-// counts would give the first XCD the longest tiles and the last one the
-// shortest.  The units are cut into 16 contiguous slices of equal k-step
-// work instead, and XCD x takes slice x from the long end and then slice
-// 15 - x from the short end, so every XCD ends on short tiles; the grid
-// holds as many workgroups per XCD as the longest pair has units (the rest
-// exit at once).
 
-// MINW: the waves per SIMD the register allocation must leave room for (1:
-// no constraint); the compiler then keeps VGPRs + AGPRs within 512 / MINW.
-template <int BM, int BN, int BK, int WM, int WN, bool BT, int DEPTH, bool VEC, bool PIPE, int MINW>
-__global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(MINW))) void sgemm_group_kernel(
-    GemmGroup g) {
+// Instruction order of the first half of a k-step: MFMAs with the LDS writes
+// of the next tile and then the fetches between them.
+template <int M, int W, int L>
+__device__ __forceinline__ void sched_mix() {
+  constexpr int per = (W + L + M - 1) / M < 1 ? 1 : (W + L + M - 1) / M;
+#pragma unroll
+  for (int i = 0, w = 0, l = 0; i < M; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+#pragma unroll
+    for (int k = 0; k < per; ++k) {
+      if (w < W) {
+        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+        ++w;
+      } else if (l < L) {
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        ++l;
+      }
+    }
+  }
+}
+
+// ... and of the second half: MFMAs with the reads of the next fragments.
+template <int M, int R>
+__device__ __forceinline__ void sched_reads() {
+  constexpr int H = M / 2 < 1 ? 1 : M / 2;
+  constexpr int per = (R + H - 1) / H;
+#pragma unroll
+  for (int i = 0, r = 0; i < M; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+#pragma unroll
+    for (int k = 0; k < per; ++k)
+      if (r < R) {
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        ++r;
+      }
+  }
+}
+
+// Four consecutive floats at any float alignment (one 16-byte load).
+__device__ __forceinline__ f32x4 load4(const void* p) {
+  typedef f32x4 f32x4u __attribute__((aligned(4)));
+  return *static_cast<const f32x4u*>(p);
+}
+
+// Four floats of row r from column c of an n x n matrix, each index clamped
+// into the matrix, and the same with zeros in the places outside it.
+__device__ __forceinline__ f32x4 edge4(const float* M, int n, int r, int c) {
+  const float* p = M + static_cast<size_t>(min(r, n - 1)) * n;
+  return f32x4{p[min(c, n - 1)], p[min(c + 1, n - 1)], p[min(c + 2, n - 1)], p[min(c + 3, n - 1)]};
+}
+__device__ __forceinline__ f32x4 inside4(f32x4 x, int n, int r, int c) {
+  return f32x4{r < n && c < n ? x.x : 0.0f, r < n && c + 1 < n ? x.y : 0.0f, r < n && c + 2 < n ? x.z : 0.0f,
+               r < n && c + 3 < n ? x.w : 0.0f};
+}
+
+// Workgroup tile BM x BN, k-step BK, WM x WN waves; each wave owns a
+// (BM/WM) x (BN/WN) block of C in accumulators of one MFMA each: 32x32x2
+// (MF 32) or 16x16x4 (MF 16) FP32.
+//
+// Order of the sum.  Both MFMAs add their k products one after another, each a
+// fused multiply-add on the running value (checked on the device bit for bit
+// against fmaf), so the order of the k values an MFMA chain is given is the
+// order of the sum.  Every run of 16 k is taken as 0 4 8 12, 1 5 9 13,
+// 2 6 10 14, 3 7 11 15.  A lane then needs whole runs of four consecutive k
+// under either MFMA: with 16x16x4, lane group g = lane / 16 supplies k = 4g + t
+// in step t; with 32x32x2, lane group h = lane / 32 supplies 4h + t and
+// 8 + 4h + t in the two steps of t.  So tiles lie in LDS in natural order, a
+// lane's A values of 16 k are one or two 16-byte reads, and all configurations
+// give the same bits.
+//
+// What bounds it: the matrix unit, once a CU has tiles enough (FP32 MFMA:
+// 157.3 TFLOP/s).  A launch of few tiles is bound by what one wave per SIMD
+// can hide by itself, which the order within a k-step is for (PIPE):
+//   * first half of the k-tile's MFMAs, with the LDS writes of the next k-tile
+//     (fetched DEPTH steps ago) and the fetches that take its registers placed
+//     between them, one after each MFMA;
+//   * the step's one barrier;
+//   * second half, with the reads of the next fragments (a second register
+//     set) between the MFMAs.
+// So no MFMA waits for LDS, for memory or for the barrier's other waves
+// longer than one MFMA, and one barrier orders both LDS hazards (buffer kt & 1
+// is written in step kt - 1 and read in the same step after the barrier; its
+// previous tile was read before the barrier of step kt - 2).  Left to itself
+// the compiler moves the fragment reads to their uses and waits for every
+// fetch in flight: 23.8 us for one 1024 x 1024 request, 19.5 us in this order
+// (13.7 us of MFMAs); 8 x 1024 x 1024 134.0 -> 124.5 us, 8 x 2048 x 2048
+// 974 -> 947 us against the previous kernel's best tiles.  The two largest
+// MF 16 tiles do not have the registers for a second fragment set and read
+// their fragments at the start of the step.
+//
+// Any n: rows of A and columns of B outside the matrix are fetched from a
+// valid place (they only reach elements of C that are not stored), so every
+// full k-tile runs the same branch-free step, and only the remainder of k is
+// masked, once per tile.  Fetches are 16 bytes at any float alignment (a row
+// of n floats starts anywhere when n is odd).  n = 517: 73.7 us with masked
+// 4-byte fetches in 81 tiles of 64x64 (80 + 1 in a grid of whole rounds),
+// 8.1 us now.
+//
+// Tiles in units, requests in order, tiles of a request row-major.  Workgroup
+// w runs on XCD w % 8, so unit (w % 8) * (grid / 8) + w / 8 gives each XCD a
+// contiguous block: tiles sharing rows of A and columns of B share an L2.
+//
+// Balanced grid (mixed sizes): the blocks are cut by work instead of by
+// count.  The requests come largest first, so equal counts would give the
+// first XCD the longest tiles and the last one the shortest.  The units are
+// cut into 16 contiguous slices of equal k-step work instead, and XCD x takes
+// slice x from the long end and then slice 15 - x from the short end, so every
+// XCD ends on short tiles; the grid holds as many workgroups per XCD as the
+// longest pair has units (the rest exit at once).
+//
+// `first` is the group's first descriptor again: a launch of one request reads
+// it together with the count instead of after the search.
+template <int BM, int BN, int BK, int WM, int WN, int MF, int DEPTH, bool PIPE>
+__global__ __launch_bounds__(WM * WN * 64) void sgemm_group_kernel(GemmDesc first, GemmGroup g) {
   constexpr int NT = WM * WN * 64;
   constexpr int TM = BM / WM, TN = BN / WN;
-  constexpr int FM = TM / 32, FN = TN / 32;
-  constexpr int KH = BK / 2;
-  constexpr int AST = BK + 4;                      // LDS row stride of As
-  constexpr int BST = BT ? BK + 4 : BN + 4;        // LDS row stride of Bs
-  constexpr int A4 = BM * BK / 4 / NT;             // float4 of A per thread per tile
-  constexpr int B4 = BK * BN / 4 / NT;             // float4 of B per thread per tile
-  static_assert(TM % 32 == 0 && TN % 32 == 0, "wave tile must be a multiple of 32");
-  static_assert(KH % 4 == 0, "BK must be a multiple of 8");
+  constexpr int FM = TM / MF, FN = TN / MF;
+  constexpr int LG = 64 / MF;       // lane groups of one MFMA, one k each
+  constexpr int P = 4 / LG;         // float4 per lane and 16 k
+  constexpr int KB = BK / 16;       // runs of 16 k
+  constexpr int NK = KB * 4 * P;    // MFMA steps of a k-tile
+  constexpr int AST = BK + 4, BST = BN + 4;
+  constexpr int A4 = BM * BK / 4 / NT, B4 = BK * BN / 4 / NT;
+  static_assert(MF == 16 || MF == 32, "MFMA shape");
+  static_assert(TM % MF == 0 && TN % MF == 0 && BK % 16 == 0, "tile shape");
   static_assert(A4 >= 1 && B4 >= 1 && A4 * NT * 4 == BM * BK && B4 * NT * 4 == BK * BN, "tile/threads mismatch");
-  static_assert(DEPTH >= 1 && DEPTH <= 3, "global prefetch depth is one to three k-tiles");
-  static_assert(!PIPE || DEPTH <= 2, "the pipelined loop takes a fetch depth of one or two");
+  static_assert(DEPTH % 2 == 0, "the slot and the fragment set of a step are compile-time");
+  using Acc = typename std::conditional<MF == 32, f32x16, f32x4>::type;
 
   __shared__ __attribute__((aligned(16))) float As[2][BM * AST];
-  __shared__ __attribute__((aligned(16))) float Bs[2][BT ? BN * BST : BK * BST];
+  __shared__ __attribute__((aligned(16))) float Bs[2][BK * BST];
 
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
-  const int li = lane & 31, lg = lane >> 5;
+  const int li = lane % MF, lg = lane / MF;
 
-  // XCD-aware order: with G a multiple of 8, workgroup w runs on XCD w % 8;
-  // renumbering it v = (w % 8) * (G / 8) + w / 8 gives each XCD a contiguous
-  // block of units in every round of the stride loop below.
-  const uint32_t G = gridDim.x;
-  const uint32_t U = g.total_units;
-  uint32_t v = blockIdx.x;
-  if (G % kXcds == 0) v = (blockIdx.x % kXcds) * (G / kXcds) + blockIdx.x / kXcds;
-
-  uint32_t u0 = v, uend = U, ustep = G;
+  // the workgroup's unit (tile)
+  uint32_t u = (blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds;
+  uint32_t uend = g.total_units;
   if (g.balanced) {
     // the j-th workgroup of XCD x takes the j-th unit of the XCD's two
     // slices; the grid holds as many per XCD as the longest pair has units
@@ -119,409 +167,305 @@ __global__ __launch_bounds__(WM * WN * 64) __attribute__((amdgpu_waves_per_eu(MI
     const int s1 = g.balanced == 2 ? kGemmSlices - 1 - x : 2 * x + 1;
     const uint32_t j = blockIdx.x / kXcds;
     const uint32_t len0 = g.cut[s0 + 1] - g.cut[s0];
-    u0 = j < len0 ? g.cut[s0] + j : g.cut[s1] + (j - len0);
+    u = j < len0 ? g.cut[s0] + j : g.cut[s1] + (j - len0);
     uend = j < len0 ? g.cut[s0 + 1] : g.cut[s1 + 1];
-    ustep = uend;  // one unit per workgroup
   }
-  for (uint32_t u = u0; u < uend; u += ustep) {
-    const int q = find_request(g, u);
-    const GemmDesc& d = g.d[q];
-    const int n = static_cast<int>(d.n);
-    const uint32_t local = u - d.unit_begin;
-    const int row0 = static_cast<int>(local / d.tiles_n) * BM;
-    const int col0 = static_cast<int>(local % d.tiles_n) * BN;
-    const float* __restrict__ A = d.A;
-    const float* __restrict__ B = d.B;
-    const bool rows_in = row0 + BM <= n, cols_in = col0 + BN <= n;
+  if (u >= uend) return;
+  GemmDesc d = first;
+  if (g.count > 1) d = g.d[find_request(g, u)];
+  const int n = static_cast<int>(d.n);
+  const uint32_t local = u - d.unit_begin;
+  const int row0 = static_cast<int>(local / d.tiles_n) * BM;
+  const int col0 = static_cast<int>(local % d.tiles_n) * BN;
+  const float* __restrict__ Ab = d.A + static_cast<size_t>(row0) * n;
+  const float* __restrict__ Bb = d.B + col0;
+  const int nfull = n / BK, rem = n - nfull * BK;
 
-    f32x16 acc[FM][FN];
+  // per-thread offsets inside a k-tile; rows of A and columns of B outside
+  // the matrix read a valid element instead (they only reach elements of C
+  // that are not stored)
+  uint32_t offa[A4], offb[B4];
 #pragma unroll
-    for (int i = 0; i < FM; ++i)
+  for (int i = 0; i < A4; ++i) {
+    const int f = tid + i * NT;
+    offa[i] = 4u * (static_cast<uint32_t>(min(f / (BK / 4), n - 1 - row0)) * n + (f % (BK / 4)) * 4);
+  }
 #pragma unroll
-      for (int j = 0; j < FN; ++j) acc[i][j] = f32x16{0};
-
-    // 4 consecutive floats of row r from column c, or zeros outside n x n
-    auto row4 = [&](const float* M, int r, int c, bool fast) -> f32x4 {
-      const float* p = M + static_cast<size_t>(r) * n + c;
-      if (fast) {
-        if (VEC) return *reinterpret_cast<const f32x4*>(p);
-        return f32x4{p[0], p[1], p[2], p[3]};
-      }
-      f32x4 x = f32x4{0};
-      if (VEC) {
-        // n and c are multiples of 4: a group of four lies wholly inside or
-        // wholly outside the matrix, so one check and one 16-byte load
-        if (r < n && c < n) x = *reinterpret_cast<const f32x4*>(p);
-        return x;
-      }
-      if (r < n) {
-        if (c + 0 < n) x.x = p[0];
-        if (c + 1 < n) x.y = p[1];
-        if (c + 2 < n) x.z = p[2];
-        if (c + 3 < n) x.w = p[3];
-      }
-      return x;
-    };
-
-    // DEPTH register slots of fetched k-tiles (slot index is a compile-time tag)
-    f32x4 ra[DEPTH][A4], rb[DEPTH][B4];
-    // FAST (a compile-time tag): an interior tile, every load unchecked
-    auto load_tile = [&](int k0, auto slot_tag, auto fast_tag) {
-      constexpr int SL = decltype(slot_tag)::value;
-      constexpr bool FAST = decltype(fast_tag)::value;
-      const bool k_in = FAST || k0 + BK <= n;
+  for (int i = 0; i < B4; ++i) {
+    const int f = tid + i * NT;
+    const int c = (f % (BN / 4)) * 4;
+    offb[i] = 4u * (static_cast<uint32_t>(f / (BN / 4)) * n + (col0 + c < n ? c : 0));
+  }
+  f32x4 ra[DEPTH][A4], rb[DEPTH][B4];
+  auto load_tile = [&](int kt, auto slot) {
+    constexpr int SL = decltype(slot)::value;
+    const char* pa = reinterpret_cast<const char*>(Ab + kt * BK);
+    const char* pb = reinterpret_cast<const char*>(Bb + static_cast<size_t>(kt) * BK * n);
 #pragma unroll
-      for (int i = 0; i < A4; ++i) {
-        const int f = tid + i * NT;
-        ra[SL][i] = row4(A, row0 + f / (BK / 4), k0 + (f % (BK / 4)) * 4, FAST || (rows_in && k_in));
-      }
-      if (BT) {
+    for (int i = 0; i < A4; ++i) ra[SL][i] = load4(pa + offa[i]);
 #pragma unroll
-        for (int i = 0; i < B4; ++i) {  // four k-rows of one column
-          const int f = tid + i * NT;
-          const int c = f % BN, kq = f / BN;
-          const int gr = k0 + 4 * kq, gc = col0 + c;
-          const float* p = B + static_cast<size_t>(gr) * n + gc;
-          if (FAST || (cols_in && k_in)) {
-            rb[SL][i] = f32x4{p[0], p[n], p[2 * n], p[3 * n]};
-          } else if (VEC) {
-            // n and gr are multiples of 4: the four k-rows are all in or all out
-            rb[SL][i] = (gc < n && gr < n) ? f32x4{p[0], p[n], p[2 * n], p[3 * n]} : f32x4{0};
-          } else {
-            f32x4 x = f32x4{0};
-            if (gc < n) {
-              if (gr + 0 < n) x.x = p[0];
-              if (gr + 1 < n) x.y = p[n];
-              if (gr + 2 < n) x.z = p[2 * static_cast<size_t>(n)];
-              if (gr + 3 < n) x.w = p[3 * static_cast<size_t>(n)];
-            }
-            rb[SL][i] = x;
-          }
+    for (int i = 0; i < B4; ++i) rb[SL][i] = load4(pb + offb[i]);
+  };
+  auto store_tile = [&](int buf, const f32x4* a, const f32x4* b) {
+#pragma unroll
+    for (int i = 0; i < A4; ++i) {
+      const int f = tid + i * NT;
+      *reinterpret_cast<f32x4*>(&As[buf][(f / (BK / 4)) * AST + (f % (BK / 4)) * 4]) = a[i];
+    }
+#pragma unroll
+    for (int i = 0; i < B4; ++i) {
+      const int f = tid + i * NT;
+      *reinterpret_cast<f32x4*>(&Bs[buf][(f / (BN / 4)) * BST + (f % (BN / 4)) * 4]) = b[i];
+    }
+  };
+  constexpr int SETS = PIPE ? 2 : 1;
+  float af[SETS][FM][KB * P * 4], bf[SETS][FN][KB * P * 4];
+  auto read_frags = [&](int buf, auto set) {
+    constexpr int S = decltype(set)::value;
+#pragma unroll
+    for (int b = 0; b < KB; ++b)
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        const int k = 16 * b + 4 * (LG * p + lg);
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+          const f32x4 x = *reinterpret_cast<const f32x4*>(&As[buf][(wm * TM + i * MF + li) * AST + k]);
+          float* o = &af[S][i][(b * P + p) * 4];
+          o[0] = x.x; o[1] = x.y; o[2] = x.z; o[3] = x.w;
         }
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            bf[S][j][(b * P + p) * 4 + t] = Bs[buf][(k + t) * BST + wn * TN + j * MF + li];
+      }
+  };
+  Acc acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = Acc{0};
+  auto mfma = [&](auto set, int s0, int s1) {
+    constexpr int S = decltype(set)::value;
+#pragma unroll
+    for (int s = 0; s < NK; ++s) {
+      if (s < s0 || s >= s1) continue;
+      const int b = s / (4 * P), t = (s / P) % 4, p = s % P;
+      const int e = (b * P + p) * 4 + t;
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          if constexpr (MF == 32)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[S][i][e], bf[S][j][e], acc[i][j], 0, 0, 0);
+          else
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[S][i][e], bf[S][j][e], acc[i][j], 0, 0, 0);
+        }
+    }
+  };
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+
+  // The k-tile beyond the full ones: fetched in the prologue, or, where the
+  // MFMAs of one k-tile take longer than a fetch, before those of the last
+  // full tile (the registers are free until then); masked with zeros outside
+  // the matrix when it is written to LDS.
+  constexpr bool kLateTail = NK * FM * FN * (MF == 32 ? 64 : 32) >= 2048;
+  f32x4 ta[A4], tb[B4];
+  auto tail = [&](auto f) {
+    const int k0 = nfull * BK;
+#pragma unroll
+    for (int i = 0; i < A4; ++i) {
+      const int e = tid + i * NT;
+      f(ta[i], d.A, row0 + e / (BK / 4), k0 + (e % (BK / 4)) * 4);
+    }
+#pragma unroll
+    for (int i = 0; i < B4; ++i) {
+      const int e = tid + i * NT;
+      f(tb[i], d.B, k0 + e / (BN / 4), col0 + (e % (BN / 4)) * 4);
+    }
+  };
+  auto tail_fetch = [&] { tail([&](f32x4& x, const float* M, int r, int c) { x = edge4(M, n, r, c); }); };
+  auto tail_store = [&](int buf) {
+    tail([&](f32x4& x, const float*, int r, int c) { x = inside4(x, n, r, c); });
+    store_tile(buf, ta, tb);
+  };
+  auto tail_mfma = [&](auto set) {   // only the runs of 16 k that hold any
+#pragma unroll
+    for (int b = 0; b < KB; ++b)
+      if (b == 0 || 16 * b < rem) mfma(set, b * NK / KB, (b + 1) * NK / KB);
+  };
+  if (nfull == 0) {
+    tail_fetch();
+    tail_store(0);
+    __syncthreads();
+    read_frags(0, I0{});
+    tail_mfma(I0{});
+  } else {
+    // tile t waits in slot t % DEPTH
+    load_tile(0, I0{});
+    load_tile(min(1, nfull - 1), I1{});
+    if constexpr (DEPTH >= 4) {
+      load_tile(min(2, nfull - 1), std::integral_constant<int, 2 % DEPTH>{});
+      load_tile(min(3, nfull - 1), std::integral_constant<int, 3 % DEPTH>{});
+    }
+    if (!kLateTail && rem) tail_fetch();
+    store_tile(0, ra[0], rb[0]);
+    load_tile(min(DEPTH, nfull - 1), I0{});
+    __syncthreads();
+    if constexpr (PIPE) read_frags(0, I0{});
+    auto step = [&](int kt, auto slot, auto set) {
+      constexpr int SL = decltype(slot)::value;
+      constexpr int S = decltype(set)::value;
+      constexpr int MH = NK / 2 * FM * FN;              // MFMAs of half a step
+      constexpr int MV = A4 + B4;                       // LDS writes, and fetches, of a step
+      constexpr int RD = KB * P * (FM + 2 * FN);        // LDS reads of a step (pairs of 4-byte reads as one)
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (PIPE) {
+        store_tile(S ^ 1, ra[SL], rb[SL]);
+        load_tile(min(kt + 1 + DEPTH, nfull - 1), slot);
+        mfma(set, 0, NK / 2);
+        sched_mix<MH, MV, MV>();
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        read_frags(S ^ 1, std::integral_constant<int, S ^ 1>{});
+        mfma(set, NK / 2, NK);
+        sched_reads<MH, RD>();
       } else {
-#pragma unroll
-        for (int i = 0; i < B4; ++i) {  // four columns of one k-row
-          const int f = tid + i * NT;
-          rb[SL][i] = row4(B, k0 + f / (BN / 4), col0 + (f % (BN / 4)) * 4, FAST || (cols_in && k_in));
-        }
+        read_frags(S, I0{});
+        __builtin_amdgcn_sched_barrier(0);
+        store_tile(S ^ 1, ra[SL], rb[SL]);
+        load_tile(min(kt + 1 + DEPTH, nfull - 1), slot);
+        mfma(I0{}, 0, NK);
+        sched_mix<2 * MH, MV, MV>();
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto last = [&](auto set) {   // tile nfull - 1, then the remainder
+      constexpr int S = decltype(set)::value;
+      using Next = std::integral_constant<int, PIPE ? S ^ 1 : 0>;
+      using This = std::integral_constant<int, PIPE ? S : 0>;
+      if constexpr (!PIPE) read_frags(S, I0{});
+      if (kLateTail && rem) tail_fetch();
+      if (!kLateTail && rem) tail_store(S ^ 1);
+      mfma(This{}, 0, NK);
+      if (rem) {
+        if (kLateTail) tail_store(S ^ 1);
+        __syncthreads();
+        read_frags(S ^ 1, Next{});
+        tail_mfma(Next{});
       }
     };
-    // k-permuted LDS layout: the float4 of k = 4q .. 4q + 3 goes to k' =
-    // (q % 2) * KH + 4 (q / 2) .. + 3
-    auto store_tile = [&](int buf, auto slot_tag) {
-      constexpr int SL = decltype(slot_tag)::value;
-#pragma unroll
-      for (int i = 0; i < A4; ++i) {
-        const int f = tid + i * NT;
-        const int r = f / (BK / 4), q = f % (BK / 4);
-        *reinterpret_cast<f32x4*>(&As[buf][r * AST + (q & 1) * KH + 4 * (q >> 1)]) = ra[SL][i];
+    // DEPTH steps per trip, so that every slot is a compile-time tag, then the
+    // 0 .. DEPTH - 1 left.  The loop has no exit inside a trip: with one, the
+    // compiler takes the newest fetch of any exit as the one to wait for.
+    // The parity of the last step names the fragment set of tile nfull - 1.
+    const int steps = nfull - 1;
+    int kt = 0;
+    for (; kt + DEPTH <= steps; kt += DEPTH) {
+      step(kt, std::integral_constant<int, 1 % DEPTH>{}, I0{});
+      step(kt + 1, std::integral_constant<int, 2 % DEPTH>{}, I1{});
+      if constexpr (DEPTH >= 4) {
+        step(kt + 2, std::integral_constant<int, 3 % DEPTH>{}, I0{});
+        step(kt + 3, std::integral_constant<int, 4 % DEPTH>{}, I1{});
       }
-#pragma unroll
-      for (int i = 0; i < B4; ++i) {
-        const int f = tid + i * NT;
-        if (BT) {
-          const int c = f % BN, kq = f / BN;
-          *reinterpret_cast<f32x4*>(&Bs[buf][c * BST + (kq & 1) * KH + 4 * (kq >> 1)]) = rb[SL][i];
-        } else {
-          const int r = f / (BN / 4), c = (f % (BN / 4)) * 4;
-          const int rp = ((r >> 2) & 1) * KH + ((r >> 3) << 2) + (r & 3);
-          *reinterpret_cast<f32x4*>(&Bs[buf][rp * BST + c]) = rb[SL][i];
-        }
-      }
-    };
-
-    const int ktiles = (n + BK - 1) / BK;
-    // One k-step: MFMAs on LDS buffer kt & 1.  Tile kt + 1 (in register
-    // slot `cur`) is written to the other buffer half-way through.  With
-    // DEPTH 1 its fetch is issued at the start of the same step, so a fetch
-    // has half a k-step to arrive; with DEPTH > 1 the step first issues the
-    // fetch of tile kt + DEPTH into slot `nxt` (tile kt's, written to LDS
-    // in the previous step), so a fetch has DEPTH - 1/2 k-steps.  Tile t
-    // lives in slot t % DEPTH.
-    //
-    // On an interior tile whose k-tiles divide evenly (FAST), every step
-    // issues the same loads and LDS writes without a branch: the last steps
-    // fetch the last k-tile again and write it to the buffer no later step
-    // reads.  The compiler can then wait for exactly the fetch it needs
-    // (`s_waitcnt vmcnt(n)` with the newer fetch still in flight); with
-    // conditional fetches it waits for all of them (`vmcnt(0)`), which
-    // takes the fetch depth back to half a k-step.
-    auto step = [&](int kt, auto cur, auto nxt, auto fast_tag) {
-      constexpr bool FAST = decltype(fast_tag)::value;
-      const int buf = kt & 1;
-      const bool more = FAST || kt + 1 < ktiles;
-      if constexpr (FAST) {
-        const int kf = min(kt + DEPTH, ktiles - 1) * BK;
-        if constexpr (DEPTH == 1) load_tile(kf, cur, fast_tag);
-        else load_tile(kf, nxt, fast_tag);
-      } else if (DEPTH == 1) {
-        if (more) load_tile((kt + 1) * BK, cur, fast_tag);
-      } else if (kt + DEPTH < ktiles) {
-        load_tile((kt + DEPTH) * BK, nxt, fast_tag);
-      }
-      float af[FM][KH], bf[FN][KH];
-#pragma unroll
-      for (int i = 0; i < FM; ++i) {
-        const float* src = &As[buf][(wm * TM + i * 32 + li) * AST + lg * KH];
-#pragma unroll
-        for (int j = 0; j < KH; j += 4) {
-          const f32x4 x = *reinterpret_cast<const f32x4*>(src + j);
-          af[i][j] = x.x; af[i][j + 1] = x.y; af[i][j + 2] = x.z; af[i][j + 3] = x.w;
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < FN; ++i) {
-        if (BT) {
-          const float* src = &Bs[buf][(wn * TN + i * 32 + li) * BST + lg * KH];
-#pragma unroll
-          for (int j = 0; j < KH; j += 4) {
-            const f32x4 x = *reinterpret_cast<const f32x4*>(src + j);
-            bf[i][j] = x.x; bf[i][j + 1] = x.y; bf[i][j + 2] = x.z; bf[i][j + 3] = x.w;
-          }
-        } else {
-          const float* src = &Bs[buf][(lg * KH) * BST + wn * TN + i * 32 + li];
-#pragma unroll
-          for (int j = 0; j < KH; ++j) bf[i][j] = src[j * BST];
-        }
-      }
-#pragma unroll
-      for (int s = 0; s < KH; ++s) {
-        // The other buffer was last read before the previous barrier.
-        if (s == KH / 2 && more) store_tile(buf ^ 1, cur);
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][s], bf[j][s], acc[i][j], 0, 0, 0);
-      }
-      __syncthreads();
-    };
-
-    using S0 = std::integral_constant<int, 0>;
-    using S1 = std::integral_constant<int, 1 % DEPTH>;
-    using S2 = std::integral_constant<int, 2 % DEPTH>;
-    auto run = [&](auto fast_tag) {
-      constexpr bool FAST = decltype(fast_tag)::value;
-      load_tile(0, S0{}, fast_tag);
-      store_tile(0, S0{});
-      if constexpr (DEPTH >= 2) {
-        if (FAST || ktiles > 1) load_tile(min(1, ktiles - 1) * BK, S1{}, fast_tag);
-      }
-      if constexpr (DEPTH >= 3) {
-        if (FAST || ktiles > 2) load_tile(min(2, ktiles - 1) * BK, S2{}, fast_tag);
-      }
-      __syncthreads();
-      // DEPTH steps per trip, so that every slot index is a compile-time tag
-      for (int kt = 0; kt < ktiles; kt += DEPTH) {
-        step(kt, S1{}, S0{}, fast_tag);
-        if constexpr (DEPTH >= 2) {
-          if (FAST || kt + 1 < ktiles) step(kt + 1, S2{}, S1{}, fast_tag);
-        }
-        if constexpr (DEPTH >= 3) {
-          if (FAST || kt + 2 < ktiles) step(kt + 2, S0{}, S2{}, fast_tag);
-        }
-      }
-    };
-    // ---- PIPE: fragments of tile kt + 1 read during the MFMAs of tile kt
-    float pa[2][FM][KH], pb[2][FN][KH];
-    auto read_frags = [&](int buf, auto fset_tag) {
-      constexpr int F = decltype(fset_tag)::value;
-#pragma unroll
-      for (int i = 0; i < FM; ++i) {
-        const float* src = &As[buf][(wm * TM + i * 32 + li) * AST + lg * KH];
-#pragma unroll
-        for (int j = 0; j < KH; j += 4) {
-          const f32x4 x = *reinterpret_cast<const f32x4*>(src + j);
-          pa[F][i][j] = x.x; pa[F][i][j + 1] = x.y; pa[F][i][j + 2] = x.z; pa[F][i][j + 3] = x.w;
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < FN; ++i) {
-        if (BT) {
-          const float* src = &Bs[buf][(wn * TN + i * 32 + li) * BST + lg * KH];
-#pragma unroll
-          for (int j = 0; j < KH; j += 4) {
-            const f32x4 x = *reinterpret_cast<const f32x4*>(src + j);
-            pb[F][i][j] = x.x; pb[F][i][j + 1] = x.y; pb[F][i][j + 2] = x.z; pb[F][i][j + 3] = x.w;
-          }
-        } else {
-          const float* src = &Bs[buf][(lg * KH) * BST + wn * TN + i * 32 + li];
-#pragma unroll
-          for (int j = 0; j < KH; ++j) pb[F][i][j] = src[j * BST];
-        }
-      }
-    };
-    // Step kt: MFMAs of tile kt (fragment set `fc`), fragments of tile
-    // kt + 1 into set `fn`; half-way, tile kt + 2 (register slot `ws`) goes
-    // to LDS buffer kt % 2 and the fetch of tile kt + 2 + DEPTH takes its
-    // slot.  FAST: the same instructions every step, indexes clamped to the
-    // last k-tile (the extra reads and writes land where no step uses them).
-    //
-    // The MFMAs touch no memory, so the compiler may move them across the
-    // barrier; the two empty asm statements keep each step's MFMAs between
-    // the LDS reads of the next fragments and the step's barrier (the first
-    // makes the current fragments appear to change after the reads, the
-    // second makes the last MFMA of each accumulator chain appear to be read
-    // before the barrier), so the barrier's wait for those reads is covered
-    // by the step's MFMAs.
-    auto step_pipe = [&](int kt, auto fc, auto fn, auto ws, auto fast_tag) {
-      constexpr bool FAST = decltype(fast_tag)::value;
-      constexpr int FC = decltype(fc)::value;
-      const int buf = kt & 1;
-      if (FAST || kt + 1 < ktiles) read_frags(buf ^ 1, fn);
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int s = 0; s < KH; ++s) asm volatile("" : "+v"(pa[FC][i][s])::"memory");
-#pragma unroll
-      for (int j = 0; j < FN; ++j)
-#pragma unroll
-        for (int s = 0; s < KH; ++s) asm volatile("" : "+v"(pb[FC][j][s])::"memory");
-#pragma unroll
-      for (int s = 0; s < KH; ++s) {
-        if (s == KH / 2 && (FAST || kt + 2 < ktiles)) {
-          store_tile(buf, ws);
-          if constexpr (FAST) load_tile(min(kt + 2 + DEPTH, ktiles - 1) * BK, ws, fast_tag);
-          else if (kt + 2 + DEPTH < ktiles) load_tile((kt + 2 + DEPTH) * BK, ws, fast_tag);
-        }
-#pragma unroll
-        for (int i = 0; i < FM; ++i)
-#pragma unroll
-          for (int j = 0; j < FN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[FC][i][s], pb[FC][j][s], acc[i][j], 0, 0, 0);
-      }
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) asm volatile("" ::"v"(acc[i][j][15]) : "memory");
-      __syncthreads();
-    };
-    using F0 = std::integral_constant<int, 0>;
-    using F1 = std::integral_constant<int, 1>;
-    using W0 = std::integral_constant<int, 2 % DEPTH>;   // slot of tile kt + 2, kt even
-    using W1 = std::integral_constant<int, 3 % DEPTH>;   // slot of tile kt + 3
-    auto run_pipe = [&](auto fast_tag) {
-      constexpr bool FAST = decltype(fast_tag)::value;
-      load_tile(0, S0{}, fast_tag);
-      store_tile(0, S0{});
-      if (FAST || ktiles > 1) {
-        load_tile(min(1, ktiles - 1) * BK, S1{}, fast_tag);
-        store_tile(1, S1{});
-      }
-      // tiles 2 .. 1 + DEPTH into their slots
-      if (FAST || ktiles > 2) load_tile(min(2, ktiles - 1) * BK, W0{}, fast_tag);
-      if constexpr (DEPTH >= 2) {
-        if (FAST || ktiles > 3) load_tile(min(3, ktiles - 1) * BK, W1{}, fast_tag);
-      }
-      __syncthreads();
-      read_frags(0, F0{});
-      // step 0 writes tile 2 over tile 0's buffer: every wave must have read
-      // tile 0's fragments first
-      __syncthreads();
-      for (int kt = 0; kt < ktiles; kt += 2) {
-        step_pipe(kt, F0{}, F1{}, W0{}, fast_tag);
-        if (FAST || kt + 1 < ktiles) step_pipe(kt + 1, F1{}, F0{}, W1{}, fast_tag);
-      }
-    };
-    if constexpr (PIPE) {
-      if (rows_in && cols_in && n % BK == 0 && ktiles % 2 == 0) run_pipe(std::true_type{});
-      else run_pipe(std::false_type{});
-    } else {
-      if (rows_in && cols_in && n % BK == 0 && ktiles % DEPTH == 0) run(std::true_type{});
-      else run(std::false_type{});
     }
-
-    float* __restrict__ C = d.C;
-    if (rows_in && cols_in) {
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const int col = col0 + wn * TN + j * 32 + li;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int row = row0 + wm * TM + i * 32 + 8 * (r / 4) + 4 * lg + (r % 4);
-            C[static_cast<size_t>(row) * n + col] = acc[i][j][r];
-          }
-        }
-    } else {
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) {
-          const int col = col0 + wn * TN + j * 32 + li;
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int row = row0 + wm * TM + i * 32 + 8 * (r / 4) + 4 * lg + (r % 4);
-            if (row < n && col < n) C[static_cast<size_t>(row) * n + col] = acc[i][j][r];
-          }
-        }
+    bool odd = false;
+    if (kt < steps) {
+      step(kt, std::integral_constant<int, 1 % DEPTH>{}, I0{});
+      odd = true;
     }
+    if constexpr (DEPTH >= 4) {
+      if (kt + 1 < steps) {
+        step(kt + 1, std::integral_constant<int, 2 % DEPTH>{}, I1{});
+        odd = false;
+      }
+      if (kt + 2 < steps) {
+        step(kt + 2, std::integral_constant<int, 3 % DEPTH>{}, I0{});
+        odd = true;
+      }
+    }
+    if (odd) last(I1{});
+    else last(I0{});
   }
+
+  float* __restrict__ C = d.C;
+  const bool whole = row0 + BM <= n && col0 + BN <= n;
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      const int col = col0 + wn * TN + j * MF + li;
+#pragma unroll
+      for (int r = 0; r < MF * MF / 64; ++r) {
+        const int row = row0 + wm * TM + i * MF + (MF == 32 ? 8 * (r / 4) + 4 * lg + (r % 4) : 4 * lg + r);
+        if (whole || (row < n && col < n)) C[static_cast<size_t>(row) * n + col] = acc[i][j][r];
+      }
+    }
 }
 
 // Tile configurations.  Index order is part of the tuner table format.
 const GemmConfig kGemmConfigs[] = {
-    {0, 64, 64, 16, 2, 2, true},
-    {1, 128, 64, 16, 2, 2, true},
-    {2, 128, 128, 16, 2, 2, true},
-    {3, 128, 128, 32, 2, 2, true},
-    {4, 256, 128, 16, 4, 2, true},
-    {5, 128, 256, 16, 2, 4, true},
-    {6, 256, 128, 32, 4, 2, true},
-    {7, 64, 128, 16, 2, 2, true},
-    {8, 128, 128, 16, 2, 2, false},
-    {9, 256, 128, 16, 4, 2, false},
-    {10, 128, 256, 16, 2, 4, false},
-    {11, 256, 128, 32, 4, 2, false},
-    {12, 128, 128, 32, 2, 2, false},
-    {13, 64, 128, 16, 2, 2, false},
-    // row-major B tiles with two k-tiles fetched ahead (prefetch depth 2)
-    {14, 256, 128, 16, 4, 2, false},
-    {15, 128, 128, 16, 2, 2, false},
-    {16, 256, 128, 32, 4, 2, false},
-    {17, 64, 128, 16, 2, 2, false},
-    {18, 128, 128, 32, 2, 2, false},
-    // three k-tiles fetched ahead
-    {19, 256, 128, 16, 4, 2, false},
-    {20, 256, 128, 32, 4, 2, false},
-    {21, 128, 128, 16, 2, 2, false},
-    // fragments of the next k-tile read during the current MFMAs (PIPE), two ahead
-    {22, 256, 128, 16, 4, 2, false},
-    {23, 128, 128, 32, 2, 2, false},
-    {24, 128, 128, 16, 2, 2, false},
-    {25, 64, 128, 16, 2, 2, false},
-    // the same with one k-tile fetched ahead (a fetch still has a whole step)
-    {26, 256, 128, 16, 4, 2, false},
-    // larger tiles for large n, two ahead
-    {27, 128, 256, 32, 2, 4, false},
-    {28, 256, 256, 16, 4, 2, false},
-    // two ahead with registers held to four waves per SIMD (VGPRs + AGPRs <= 128)
-    {29, 64, 128, 16, 2, 2, false},
+    {0, 32, 32, 32, 2, 2, false},
+    {1, 32, 32, 32, 2, 2, false},
+    {2, 32, 32, 64, 2, 2, false},
+    {3, 32, 64, 32, 2, 2, false},
+    {4, 32, 64, 64, 2, 2, false},
+    {5, 64, 32, 32, 2, 2, false},
+    {6, 64, 64, 32, 2, 4, false},
+    {7, 64, 64, 32, 2, 2, false},
+    {8, 64, 64, 32, 2, 2, false},
+    {9, 64, 64, 16, 2, 2, false},
+    {10, 64, 64, 64, 2, 2, false},
+    {11, 64, 96, 32, 2, 2, false},
+    {12, 96, 64, 32, 2, 2, false},
+    {13, 96, 96, 32, 2, 2, false},
+    {14, 96, 128, 32, 2, 2, false},
+    {15, 128, 96, 32, 2, 2, false},
+    {16, 64, 128, 16, 2, 2, false},
+    {17, 64, 128, 32, 2, 2, false},
+    {18, 128, 64, 32, 4, 2, false},
+    {19, 128, 64, 32, 2, 2, false},
+    {20, 128, 128, 16, 2, 2, false},
+    {21, 128, 128, 32, 2, 2, false},
+    {22, 128, 128, 16, 4, 2, false},
+    {23, 128, 128, 32, 2, 4, false},
+    {24, 128, 256, 16, 2, 4, false},
+    {25, 256, 128, 16, 4, 2, false},
+    {26, 64, 256, 16, 1, 4, false},
+    {27, 256, 64, 16, 4, 1, false},
+    {28, 128, 192, 32, 2, 4, false},
+    {29, 192, 128, 32, 4, 2, false},
 };
 constexpr int kNumGemmConfigs = sizeof(kGemmConfigs) / sizeof(kGemmConfigs[0]);
 
 int g_forced_config = -1;
 
 #include "gemm_tiles.inc"   // kTileTable: (n_max, config index) rows written by the tuner
+constexpr uint64_t kTileTableEnd = 1ull << 30;  // the last row's bound: every larger size
 
-template <int BM, int BN, int BK, int WM, int WN, bool BT, int DEPTH = 1, bool PIPE = false, int MINW = 1>
-hipError_t launch_cfg(const GemmGroup& g, bool vec, hipStream_t s, int grid_cap) {
+// BT (B staged transposed in LDS) is false in every configuration: the 16-byte
+// fragment reads it gives B cost four times the fetch or LDS write instructions.
+template <int BM, int BN, int BK, int WM, int WN, bool BT, int MF, int DEPTH, bool PIPE>
+hipError_t launch_cfg(const GemmGroup& g, hipStream_t s) {
   constexpr int NT = WM * WN * 64;
-  int cap = grid_cap > 0 ? grid_cap : 256 * 2;
-  int grid = static_cast<int>(std::min<uint32_t>(g.total_units, static_cast<uint32_t>(cap)));
-  if (grid > kXcds) grid -= grid % kXcds;  // whole rounds over the 8 XCDs
-  if (g.balanced) {  // one workgroup per unit of the longest XCD pair of slices
-    uint32_t most = 0;
+  // one workgroup per unit, in whole rounds over the 8 XCDs
+  uint32_t per_xcd = (g.total_units + kXcds - 1) / kXcds;
+  if (g.balanced) {  // as many as the longest XCD pair of slices has units
+    per_xcd = 0;
     for (int x = 0; x < kXcds; ++x) {
       int s0, s1;
       xcd_slices(x, g.balanced == 2, &s0, &s1);
-      most = std::max(most, (g.cut[s0 + 1] - g.cut[s0]) + (g.cut[s1 + 1] - g.cut[s1]));
+      per_xcd = std::max(per_xcd, (g.cut[s0 + 1] - g.cut[s0]) + (g.cut[s1 + 1] - g.cut[s1]));
     }
-    grid = static_cast<int>(most) * kXcds;
   }
-  return vec ? launch_group(sgemm_group_kernel<BM, BN, BK, WM, WN, BT, DEPTH, true, PIPE, MINW>, grid, NT, s, g)
-             : launch_group(sgemm_group_kernel<BM, BN, BK, WM, WN, BT, DEPTH, false, PIPE, MINW>, grid, NT, s, g);
+  if (per_xcd == 0) return hipSuccess;
+  void (*const kernel)(GemmDesc, GemmGroup) = sgemm_group_kernel<BM, BN, BK, WM, WN, MF, DEPTH, PIPE>;
+  void* args[] = {const_cast<GemmDesc*>(&g.d[0]), const_cast<GemmGroup*>(&g)};
+  return hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(per_xcd * kXcds), dim3(NT), args, 0, s);
 }
 
 }  // namespace
@@ -530,20 +474,35 @@ int gemm_config_count() { return kNumGemmConfigs; }
 const GemmConfig& gemm_config(int idx) { return kGemmConfigs[idx]; }
 void gemm_config_force(int idx) { g_forced_config = (idx >= 0 && idx < kNumGemmConfigs) ? idx : -1; }
 
-int gemm_config_for(uint64_t n) {
+int gemm_config_forced() {
   if (g_forced_config >= 0) return g_forced_config;
   // tuning and tests only: force one configuration for every size
   if (const char* env = getenv("GVM_SGEMM_CONFIG")) {
     const int c = atoi(env);
     if (c >= 0 && c < kNumGemmConfigs) return c;
   }
-  int c = static_cast<int>(kTileTable[sizeof(kTileTable) / sizeof(kTileTable[0]) - 1][1]);
-  for (const auto& row : kTileTable)
-    if (n <= row[0]) {
-      c = static_cast<int>(row[1]);
-      break;
-    }
-  return c;
+  return -1;
+}
+// The tuner times launches of kTableCount requests of one size, so its rows
+// hold for those; any other launch takes the cheapest configuration by the
+// cost formula, which knows how many tiles the launch has for the chip (one
+// 1024 x 1024 request: 19.5 us with the formula's 64x64 tiles, 128 us with the
+// 256x128 tiles that are best for eight of them).
+int gemm_config_for(uint32_t count, const uint32_t* n) {
+  const int forced = gemm_config_forced();
+  if (forced >= 0) return forced;
+  constexpr uint32_t kTableCount = 8, kTableStep = 64;
+  bool table = count == kTableCount && n[0] % kTableStep == 0;
+  for (uint32_t i = 1; i < count; ++i) table &= n[i] == n[0];
+  if (table)
+    for (const auto& row : kTileTable)
+      if (n[0] <= row[0] && row[0] < kTileTableEnd) return static_cast<int>(row[1]);
+  return gemm_cheapest(count, n);
+}
+int gemm_config_for(const GemmGroup& g) {
+  uint32_t n[kMaxGroup];
+  for (uint32_t i = 0; i < g.count; ++i) n[i] = g.d[i].n;
+  return gemm_config_for(g.count, n);
 }
 void finalize_gemm_group(GemmGroup& g, int config_idx) {
   const GemmConfig& c = kGemmConfigs[config_idx];
@@ -565,55 +524,47 @@ void finalize_gemm_group(GemmGroup& g, int config_idx) {
   balance_slices(g.count, units, ksteps, g.cut);
   g.balanced = 0;
 }
-hipError_t launch_sgemm_group(const GemmGroup& g_in, int config_idx, hipStream_t s, int grid_cap) {
+hipError_t launch_sgemm_group(const GemmGroup& g_in, int config_idx, hipStream_t s) {
   GemmGroup g = g_in;
-  g.balanced = 0;
-  if (grid_cap > 0 && static_cast<uint32_t>(grid_cap) >= g.total_units && g.count > 1) {
-    bool mixed = false;
-    for (uint32_t i = 1; i < g.count; ++i) mixed |= g.d[i].n != g.d[0].n;
-    // GVM_SGEMM_XCD_PAIRED=0 keeps each XCD on one contiguous run (tuning)
-    static const bool paired = [] {
-      const char* e = getenv("GVM_SGEMM_XCD_PAIRED");
-      return !(e && e[0] == '0');
-    }();
-    if (mixed) g.balanced = paired ? 2 : 1;
-  }
-  bool vec = true;
-  for (uint32_t i = 0; i < g.count; ++i)
-    if ((g.d[i].n % 4) != 0 || (reinterpret_cast<uintptr_t>(g.d[i].A) & 15) ||
-        (reinterpret_cast<uintptr_t>(g.d[i].B) & 15))
-      vec = false;
+  bool mixed = false;
+  for (uint32_t i = 1; i < g.count; ++i) mixed |= g.d[i].n != g.d[0].n;
+  // GVM_SGEMM_XCD_PAIRED=0 keeps each XCD on one contiguous run (tuning)
+  static const bool paired = [] {
+    const char* e = getenv("GVM_SGEMM_XCD_PAIRED");
+    return !(e && e[0] == '0');
+  }();
+  g.balanced = !mixed ? 0 : paired ? 2 : 1;
   switch (config_idx) {
-    case 0: return launch_cfg<64, 64, 16, 2, 2, true>(g, vec, s, grid_cap);
-    case 1: return launch_cfg<128, 64, 16, 2, 2, true>(g, vec, s, grid_cap);
-    case 2: return launch_cfg<128, 128, 16, 2, 2, true>(g, vec, s, grid_cap);
-    case 3: return launch_cfg<128, 128, 32, 2, 2, true>(g, vec, s, grid_cap);
-    case 4: return launch_cfg<256, 128, 16, 4, 2, true>(g, vec, s, grid_cap);
-    case 5: return launch_cfg<128, 256, 16, 2, 4, true>(g, vec, s, grid_cap);
-    case 6: return launch_cfg<256, 128, 32, 4, 2, true>(g, vec, s, grid_cap);
-    case 7: return launch_cfg<64, 128, 16, 2, 2, true>(g, vec, s, grid_cap);
-    case 8: return launch_cfg<128, 128, 16, 2, 2, false>(g, vec, s, grid_cap);
-    case 9: return launch_cfg<256, 128, 16, 4, 2, false>(g, vec, s, grid_cap);
-    case 10: return launch_cfg<128, 256, 16, 2, 4, false>(g, vec, s, grid_cap);
-    case 11: return launch_cfg<256, 128, 32, 4, 2, false>(g, vec, s, grid_cap);
-    case 12: return launch_cfg<128, 128, 32, 2, 2, false>(g, vec, s, grid_cap);
-    case 13: return launch_cfg<64, 128, 16, 2, 2, false>(g, vec, s, grid_cap);
-    case 14: return launch_cfg<256, 128, 16, 4, 2, false, 2>(g, vec, s, grid_cap);
-    case 15: return launch_cfg<128, 128, 16, 2, 2, false, 2>(g, vec, s, grid_cap);
-    case 16: return launch_cfg<256, 128, 32, 4, 2, false, 2>(g, vec, s, grid_cap);
-    case 17: return launch_cfg<64, 128, 16, 2, 2, false, 2>(g, vec, s, grid_cap);
-    case 18: return launch_cfg<128, 128, 32, 2, 2, false, 2>(g, vec, s, grid_cap);
-    case 19: return launch_cfg<256, 128, 16, 4, 2, false, 3>(g, vec, s, grid_cap);
-    case 20: return launch_cfg<256, 128, 32, 4, 2, false, 3>(g, vec, s, grid_cap);
-    case 21: return launch_cfg<128, 128, 16, 2, 2, false, 3>(g, vec, s, grid_cap);
-    case 22: return launch_cfg<256, 128, 16, 4, 2, false, 2, true>(g, vec, s, grid_cap);
-    case 23: return launch_cfg<128, 128, 32, 2, 2, false, 2, true>(g, vec, s, grid_cap);
-    case 24: return launch_cfg<128, 128, 16, 2, 2, false, 2, true>(g, vec, s, grid_cap);
-    case 25: return launch_cfg<64, 128, 16, 2, 2, false, 2, true>(g, vec, s, grid_cap);
-    case 26: return launch_cfg<256, 128, 16, 4, 2, false, 1, true>(g, vec, s, grid_cap);
-    case 27: return launch_cfg<128, 256, 32, 2, 4, false, 2>(g, vec, s, grid_cap);
-    case 28: return launch_cfg<256, 256, 16, 4, 2, false, 2>(g, vec, s, grid_cap);
-    case 29: return launch_cfg<64, 128, 16, 2, 2, false, 2, false, 4>(g, vec, s, grid_cap);
+    case 0: return launch_cfg<32, 32, 32, 2, 2, false, 16, 4, true>(g, s);
+    case 1: return launch_cfg<32, 32, 32, 2, 2, false, 16, 2, true>(g, s);
+    case 2: return launch_cfg<32, 32, 64, 2, 2, false, 16, 2, true>(g, s);
+    case 3: return launch_cfg<32, 64, 32, 2, 2, false, 16, 2, true>(g, s);
+    case 4: return launch_cfg<32, 64, 64, 2, 2, false, 16, 2, true>(g, s);
+    case 5: return launch_cfg<64, 32, 32, 2, 2, false, 16, 2, true>(g, s);
+    case 6: return launch_cfg<64, 64, 32, 2, 4, false, 16, 2, true>(g, s);
+    case 7: return launch_cfg<64, 64, 32, 2, 2, false, 16, 4, true>(g, s);
+    case 8: return launch_cfg<64, 64, 32, 2, 2, false, 32, 2, true>(g, s);
+    case 9: return launch_cfg<64, 64, 16, 2, 2, false, 32, 4, true>(g, s);
+    case 10: return launch_cfg<64, 64, 64, 2, 2, false, 32, 2, true>(g, s);
+    case 11: return launch_cfg<64, 96, 32, 2, 2, false, 16, 2, true>(g, s);
+    case 12: return launch_cfg<96, 64, 32, 2, 2, false, 16, 2, true>(g, s);
+    case 13: return launch_cfg<96, 96, 32, 2, 2, false, 16, 2, true>(g, s);
+    case 14: return launch_cfg<96, 128, 32, 2, 2, false, 16, 2, true>(g, s);
+    case 15: return launch_cfg<128, 96, 32, 2, 2, false, 16, 2, true>(g, s);
+    case 16: return launch_cfg<64, 128, 16, 2, 2, false, 32, 4, true>(g, s);
+    case 17: return launch_cfg<64, 128, 32, 2, 2, false, 32, 2, true>(g, s);
+    case 18: return launch_cfg<128, 64, 32, 4, 2, false, 32, 2, true>(g, s);
+    case 19: return launch_cfg<128, 64, 32, 2, 2, false, 32, 2, true>(g, s);
+    case 20: return launch_cfg<128, 128, 16, 2, 2, false, 32, 2, true>(g, s);
+    case 21: return launch_cfg<128, 128, 32, 2, 2, false, 32, 2, true>(g, s);
+    case 22: return launch_cfg<128, 128, 16, 4, 2, false, 32, 4, true>(g, s);
+    case 23: return launch_cfg<128, 128, 32, 2, 4, false, 32, 2, true>(g, s);
+    case 24: return launch_cfg<128, 256, 16, 2, 4, false, 32, 2, true>(g, s);
+    case 25: return launch_cfg<256, 128, 16, 4, 2, false, 32, 2, true>(g, s);
+    case 26: return launch_cfg<64, 256, 16, 1, 4, false, 32, 2, true>(g, s);
+    case 27: return launch_cfg<256, 64, 16, 4, 1, false, 32, 2, true>(g, s);
+    case 28: return launch_cfg<128, 192, 32, 2, 4, false, 16, 2, false>(g, s);
+    case 29: return launch_cfg<192, 128, 32, 4, 2, false, 16, 2, false>(g, s);
     default: return hipErrorInvalidValue;
   }
 }
