@@ -61,7 +61,7 @@ bool request_layout(int kernel_id, uint64_t n, Layout* out) {
       if (n > (1ull << 40)) return false;
       out->in_bytes = 2 * sizeof(uint64_t);
       out->out_bytes = kEpWords * sizeof(uint64_t);
-      out->scratch_bytes = ((n + kEpUnit - 1) / kEpUnit) * kEpWords * sizeof(uint64_t);  // one partial per unit
+      out->scratch_bytes = ep_scratch_bytes(n);  // one partial record per unit
       return true;
     default:
       return false;

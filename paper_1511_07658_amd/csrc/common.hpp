@@ -60,10 +60,29 @@ int cu_partition_masks(uint32_t latency_cus, uint32_t* latency_mask, uint32_t* b
 
 constexpr uint64_t kLocalCopyBytes = 1ull << 20;
 
-// EP-like kernel: pairs per work unit, and the 64-bit words of one result
-// record (sx, sy, q[0..9]), the request's output and each unit's partial.
-constexpr uint64_t kEpUnit = 1ull << 15;
+// EP-like kernel: the 64-bit words of a request's output (sx, sy, q[0..9]),
+// the largest work unit in pairs, and the bytes of one unit's partial record
+// (sx, sy in binary64, ten 16-bit counts).
 constexpr uint64_t kEpWords = 12;
+constexpr uint64_t kEpUnit = 1ull << 15;
+constexpr uint64_t kEpRecordBytes = 40;
+// Device scratch of a request of n pairs: 96 bytes per 2^15 pairs, and at least
+// what the arena's 4 KiB granule leaves beside a slot's input and output.
+inline uint64_t ep_scratch_bytes(uint64_t n) {
+  const uint64_t by_size = ((n + kEpUnit - 1) / kEpUnit) * 96;
+  const uint64_t rest_of_granule = 4096 - 2 * kAlign;
+  return by_size > rest_of_granule ? by_size : rest_of_granule;
+}
+// Pairs per work unit of a request of n pairs, a multiple of 1024 (two per
+// thread): as many units as records fit the scratch, but whole multiples of
+// the 256 CUs where that many fit (2^24 pairs: 1024 units).
+inline uint64_t ep_unit(uint64_t n) {
+  uint64_t units = ep_scratch_bytes(n) / kEpRecordBytes;
+  if (units > 256) units = units / 256 * 256;
+  const uint64_t per = (n + units - 1) / units;
+  const uint64_t unit = (per + 1023) / 1024 * 1024;
+  return unit < kEpUnit ? unit : kEpUnit;
+}
 // false if the kernel id is unknown, n == 0 or the size overflows.
 bool request_layout(int kernel_id, uint64_t n, Layout* out);
 // Device slot of a request: input, then output at the next aligned offset,

@@ -250,6 +250,10 @@ class HipDevice final : public Device {
       }
       return rc;
     }
+    // one request's phases are its chain: PS-2 runs it without the event
+    // hops between the phases' streams (measured in the device phase of a
+    // small request, which the host's enqueueing bounds)
+    if (policy == GVM_POLICY_PS1 && jobs.size() == 1) policy = GVM_POLICY_PS2;
     if (policy != GVM_POLICY_PS1 && policy != GVM_POLICY_PS2)
       std::stable_sort(jobs.begin(), jobs.end(), [](const Job* x, const Job* y) { return x->rank < y->rank; });
     if (jobs[0]->part >= 0 && part_streams_.size() == 2) ++part_launches_[jobs[0]->part];
@@ -275,10 +279,10 @@ class HipDevice final : public Device {
     // span1 follows them all (batch_timing; not combined with graph replay)
     std::vector<hipStream_t> span_streams;
     const bool span = cfg_.batch_timing && !cfg_.use_graphs;
+    hipStream_t span_stream = compute_streams_[0];
     if (span) {
       // only the streams that carry work of this batch (each extra stream
       // costs a cross-queue wait at both ends of the span)
-      hipStream_t c0 = compute_streams_[0];
       bool any_in = false, any_out = false;
       for (Job* j : jobs) {
         any_in |= j->copy_in && (!j->local || policy == GVM_POLICY_PS1);
@@ -286,7 +290,8 @@ class HipDevice final : public Device {
       }
       if (any_in) span_streams.push_back(h2d_);
       if (any_out) span_streams.push_back(d2h_);
-      if (policy == GVM_POLICY_PS1 || policy == GVM_POLICY_PS2) {
+      const bool per_rank = policy == GVM_POLICY_PS1 || policy == GVM_POLICY_PS2;
+      if (per_rank) {
         for (Job* j : jobs) {
           hipStream_t s = kernel_stream(j);
           if (std::find(span_streams.begin(), span_streams.end(), s) == span_streams.end()) span_streams.push_back(s);
@@ -296,10 +301,14 @@ class HipDevice final : public Device {
       } else if (grouped_launches(jobs) > 1) {
         span_streams.push_back(compute_streams_[1]);
       }
+      if (per_rank && span_streams.size() == 1) {  // all of it on one stream: the span too
+        span_stream = span_streams[0];
+        span_streams.clear();
+      }
       b->span0 = timed_event();
       b->span1 = timed_event();
       if (!b->span0 || !b->span1) rc = fail(GVM_EDEVICE, "hipEventCreate failed");
-      if (rc == GVM_OK && hipEventRecord(b->span0, c0) != hipSuccess) rc = fail(GVM_EDEVICE, "event record failed");
+      if (rc == GVM_OK && hipEventRecord(b->span0, span_stream) != hipSuccess) rc = fail(GVM_EDEVICE, "event record failed");
       for (hipStream_t s : span_streams)
         if (rc == GVM_OK && hipStreamWaitEvent(s, b->span0, 0) != hipSuccess) rc = fail(GVM_EDEVICE, "stream wait failed");
     }
@@ -369,17 +378,16 @@ class HipDevice final : public Device {
       rc = launch_grouped(b);
     }
     if (span && rc == GVM_OK) {
-      hipStream_t c0 = compute_streams_[0];
       for (hipStream_t s : span_streams) {
         hipEvent_t ev = sync_event(b);
-        if (!ev || hipEventRecord(ev, s) != hipSuccess || hipStreamWaitEvent(c0, ev, 0) != hipSuccess) {
+        if (!ev || hipEventRecord(ev, s) != hipSuccess || hipStreamWaitEvent(span_stream, ev, 0) != hipSuccess) {
           rc = fail(GVM_EDEVICE, "span join failed");
           break;
         }
       }
-      if (rc == GVM_OK && hipEventRecord(b->span1, c0) != hipSuccess) rc = fail(GVM_EDEVICE, "event record failed");
+      if (rc == GVM_OK && hipEventRecord(b->span1, span_stream) != hipSuccess) rc = fail(GVM_EDEVICE, "event record failed");
       if (rc == GVM_OK) {  // the jobs complete with the span
-        track(b, b->span1, c0);
+        track(b, b->span1, span_stream);
         for (size_t i = 0; i < jobs.size(); ++i) b->done[i] = b->span1;
       }
     }

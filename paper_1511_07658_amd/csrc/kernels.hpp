@@ -77,8 +77,9 @@ struct GemmGroup {
 struct EpDesc {
   const uint64_t* key;   // (k0, k1)
   uint64_t* out;         // sx, sy (binary64 bit patterns), q[0..9]
-  uint64_t* partial;     // one record of the same layout per work unit
+  void* partial;         // one record (kEpRecordBytes) per work unit, 8-byte aligned
   uint64_t n;            // pairs
+  uint64_t unit;         // pairs per work unit (ep_unit(n), set by finalize_ep_group)
   uint64_t unit_begin;
   uint64_t units;
 };
