@@ -748,7 +748,6 @@ class HipDevice final : public Device {
         vg.d[i].c = reinterpret_cast<float*>(v[i]->slot + slot_out_offset(v[i]->lay));
         vg.d[i].n = v[i]->req.n;
       }
-      finalize_vec_group(vg);
       if ((e = mark()) == hipSuccess) e = (k == GVM_K_VECADD) ? launch_vecadd_group(vg, s) : launch_vecmul_group(vg, s);
     } else if (k == GVM_K_BLACKSCHOLES) {
       BsGroup bg{};
@@ -766,7 +765,6 @@ class HipDevice final : public Device {
         bg.d[i].put = out + n;
         bg.d[i].n = n;
       }
-      finalize_bs_group(bg);
       if ((e = mark()) == hipSuccess) e = launch_bs_group(bg, s);
     } else if (k == GVM_K_SGEMM) {
       GemmGroup gg{};
@@ -1027,7 +1025,6 @@ class HipDevice final : public Device {
     VecGroup vg{};
     vg.count = 1;
     vg.d[0] = VecDesc{base, base + 64, base + 128, 64, 0};
-    finalize_vec_group(vg);
     HIPCHK(launch_vecadd_group(vg, s));
     HIPCHK(launch_vecmul_group(vg, s));
     BsGroup bg{};
@@ -1035,7 +1032,6 @@ class HipDevice final : public Device {
     bg.rate = cfg_.bs_rate;
     bg.volatility = cfg_.bs_volatility;
     bg.d[0] = BsDesc{base, base + 64, base + 128, base + 192, base + 256, 64, 0};
-    finalize_bs_group(bg);
     HIPCHK(launch_bs_group(bg, s));
     for (int c = 0; c < gemm_config_count(); ++c) {
       GemmGroup gg{};

@@ -113,25 +113,19 @@ int gemm_config_forced();
 // Override the table (tuner only): config index for every n, or -1 to restore.
 void gemm_config_force(int idx);
 
-constexpr uint64_t kVecUnit = 4096;   // elements per vector work unit
-constexpr uint64_t kBsUnit = 4096;    // options per Black-Scholes work unit (the launcher
-                                      // recounts the units for its launch shape)
-
-// Persistent-grid launchers.  `grid_cap` bounds the number of workgroups
-// (0 = default for the kernel).  Return hipSuccess or the launch error.
-hipError_t launch_vecadd_group(const VecGroup& g, hipStream_t s, int grid_cap = 0);
-hipError_t launch_vecmul_group(const VecGroup& g, hipStream_t s, int grid_cap = 0);
-hipError_t launch_bs_group(const BsGroup& g, hipStream_t s, int grid_cap = 0);
+// Launchers of the streaming kernels: they cut the requests into work units
+// for the launch (unit_begin, total_units).  Return hipSuccess or the error.
+hipError_t launch_vecadd_group(const VecGroup& g, hipStream_t s);
+hipError_t launch_vecmul_group(const VecGroup& g, hipStream_t s);
+hipError_t launch_bs_group(const BsGroup& g, hipStream_t s);
 // One workgroup per tile; for a group of mixed sizes the tiles are spread over
 // the XCDs by their k-steps (GemmGroup.cut) instead of by count.
 hipError_t launch_sgemm_group(const GemmGroup& g, int config_idx, hipStream_t s);
 // EP-like tally: one launch over the work units of every request (partials),
 // then one workgroup per request sums its partials.
-hipError_t launch_ep_group(const EpGroup& g, hipStream_t s, int grid_cap = 0);
+hipError_t launch_ep_group(const EpGroup& g, hipStream_t s);
 
 // Fill the unit bookkeeping of a group (unit_begin, tiles, totals).
-void finalize_vec_group(VecGroup& g);
-void finalize_bs_group(BsGroup& g);
 void finalize_gemm_group(GemmGroup& g, int config_idx);
 void finalize_ep_group(EpGroup& g);
 

@@ -52,7 +52,6 @@ extern "C" int gvm_plain_run(int kernel_id, const void* in, void* out, uint64_t 
     gvm::VecGroup g{};
     g.count = 1;
     g.d[0] = gvm::VecDesc{fin, fin + n, fout, n, 0};
-    gvm::finalize_vec_group(g);
     e = kernel_id == GVM_K_VECADD ? gvm::launch_vecadd_group(g, nullptr) : gvm::launch_vecmul_group(g, nullptr);
   } else if (kernel_id == GVM_K_BLACKSCHOLES) {
     gvm::BsGroup g{};
@@ -60,7 +59,6 @@ extern "C" int gvm_plain_run(int kernel_id, const void* in, void* out, uint64_t 
     g.rate = bs_rate;
     g.volatility = bs_volatility;
     g.d[0] = gvm::BsDesc{fin, fin + n, fin + 2 * n, fout, fout + n, n, 0};
-    gvm::finalize_bs_group(g);
     e = gvm::launch_bs_group(g, nullptr);
   } else if (kernel_id == GVM_K_EP) {
     gvm::EpGroup g{};

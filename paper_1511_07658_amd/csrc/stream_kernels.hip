@@ -4,32 +4,33 @@
 //  * Black-Scholes call + put (Table 3 "BlackScholes"): HBM-bound with a
 //    transcendental-heavy body.
 //
-// Both are grouped persistent launches: one grid walks the work units (vector
-// chunks) of every request of the group; the unit -> request map is a search
-// over the per-request first unit held in the kernel arguments.  A unit is
-// always computed by the same code in the same order, whatever else is in the
-// group, so a rank's output is bit-identical alone and in the mix.
+// Both are grouped launches: one grid walks the work units (vector chunks) of
+// every request of the group; the unit -> request map is a search over the
+// per-request first unit held in the kernel arguments.  An element is always
+// computed by the same operations, whatever unit it falls into and whatever
+// else is in the group, so a rank's output is bit-identical alone and in the
+// mix.
 #include "group_device.hpp"
 
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 
 namespace gvm {
 
 namespace {
 
-// Launch shapes measured on the MI355X (sweeps of grid, float4 per thread
-// and cache policy over the grouped launches): one workgroup per work unit
-// beats every persistent grid (512 to 4096 workgroups) for groups beyond the
-// memory-side cache, since the dispatcher keeps every SIMD at its register-
-// limited occupancy and balances the tail; for small groups the two
-// coincide.  A group whose bytes exceed the 256 MB memory-side cache
-// streams through with non-temporal loads and stores; a smaller one stays
-// cacheable, since its inputs come back from that cache on the next request.
-constexpr int kVecGrid = 1 << 24;     // i.e. one workgroup per unit
-constexpr int kBsGrid = 1 << 24;
-constexpr int kBsV4 = 4;              // float4 per thread per stream of a Black-Scholes unit
-constexpr uint64_t kMallBytes = 256ull << 20;
+// Launch shape, measured on the MI355X (float4 per thread and cache policy,
+// 0.26M to 268M elements; three buffers in turn, and one read again).  One
+// workgroup per work unit: the dispatcher keeps every SIMD at its
+// register-limited occupancy and balances the tail.  Results are stored
+// non-temporal at any size: nothing here reads them back, and the 256 MB
+// memory-side cache keeps the inputs instead (vector add of 2^22 read again:
+// 6.9 us, 8.4 with cached stores).  Inputs are loaded cached up to kCachedInput
+// bytes, with 2 float4 per thread (8M elements 15.2 us, 16.7 non-temporal);
+// beyond it non-temporal with 4 (16M: 31.8 us, 35.0 cached; 14.5M 27.6 and
+// 30.0; at 12.6M, 100 MB of input, the two meet).
+constexpr uint64_t kCachedInput = 96ull << 20;
 
 // ---------------------------------------------------------------- vectors
 
@@ -42,44 +43,48 @@ __device__ __forceinline__ T stream_load(const T* p) {
   else return *p;
 }
 
-template <class T, bool NT>
-__device__ __forceinline__ void stream_store(T v, T* p) {
-  if constexpr (NT) __builtin_nontemporal_store(v, p);
-  else *p = v;
+template <class T>
+__device__ __forceinline__ void stream_store(T v, T* p) { __builtin_nontemporal_store(v, p); }
+
+// Four consecutive floats at any float alignment: one 16-byte access.
+typedef f32x4 f32x4u __attribute__((aligned(4)));
+
+template <class Op>
+__device__ __forceinline__ f32x4 op4(Op op, f32x4 a, f32x4 b) {
+  return f32x4{op(a.x, b.x), op(a.y, b.y), op(a.z, b.z), op(a.w, b.w)};
 }
 
-template <class Op, bool NT>
+// Bound by memory.  The operands of a request of odd length start anywhere
+// (b is a + n), so every access is 16 bytes at float alignment: 14.5M elements
+// 27.6 us (6.3 TB/s, as 2^24 has), 34.8 element by element.
+template <class Op, int V4, bool NT>
 __global__ __launch_bounds__(kThreads) void vec_group_kernel(VecGroup g) {
-  constexpr int kV4 = kVecUnit / 4 / kThreads;  // float4 per thread per unit
+  constexpr uint64_t kUnit = V4 * 4 * kThreads;
   Op op;
   for (uint64_t u = blockIdx.x; u < g.total_units; u += gridDim.x) {
-    const int r = find_request(g, u);
-    const VecDesc& d = g.d[r];
-    const uint64_t e0 = (u - d.unit_begin) * kVecUnit;
-    const uint64_t e1 = min(e0 + kVecUnit, d.n);
-    const bool aligned = ((reinterpret_cast<uintptr_t>(d.a) | reinterpret_cast<uintptr_t>(d.b) |
-                           reinterpret_cast<uintptr_t>(d.c)) & 15) == 0;
-    if (aligned && e1 - e0 == kVecUnit) {
-      const f32x4* a4 = reinterpret_cast<const f32x4*>(d.a + e0);
-      const f32x4* b4 = reinterpret_cast<const f32x4*>(d.b + e0);
-      f32x4* c4 = reinterpret_cast<f32x4*>(d.c + e0);
-      f32x4 va[kV4], vb[kV4];
+    const VecDesc& d = g.d[find_request(g, u)];
+    const uint64_t e0 = (u - d.unit_begin) * kUnit;
+    const uint64_t left = d.n - e0;
+    const f32x4u* a4 = reinterpret_cast<const f32x4u*>(d.a + e0);
+    const f32x4u* b4 = reinterpret_cast<const f32x4u*>(d.b + e0);
+    f32x4u* c4 = reinterpret_cast<f32x4u*>(d.c + e0);
+    if (left >= kUnit) {
+      f32x4 va[V4], vb[V4];
 #pragma unroll
-      for (int j = 0; j < kV4; ++j) {
-        va[j] = stream_load<f32x4, NT>(a4 + threadIdx.x + j * kThreads);
-        vb[j] = stream_load<f32x4, NT>(b4 + threadIdx.x + j * kThreads);
+      for (int j = 0; j < V4; ++j) {
+        va[j] = stream_load<f32x4u, NT>(a4 + threadIdx.x + j * kThreads);
+        vb[j] = stream_load<f32x4u, NT>(b4 + threadIdx.x + j * kThreads);
       }
 #pragma unroll
-      for (int j = 0; j < kV4; ++j) {
-        f32x4 c;
-        c.x = op(va[j].x, vb[j].x);
-        c.y = op(va[j].y, vb[j].y);
-        c.z = op(va[j].z, vb[j].z);
-        c.w = op(va[j].w, vb[j].w);
-        stream_store<f32x4, NT>(c, c4 + threadIdx.x + j * kThreads);
-      }
+      for (int j = 0; j < V4; ++j) stream_store<f32x4u>(op4(op, va[j], vb[j]), c4 + threadIdx.x + j * kThreads);
     } else {
-      for (uint64_t e = e0 + threadIdx.x; e < e1; e += kThreads) d.c[e] = op(d.a[e], d.b[e]);
+      for (uint64_t e = 4 * threadIdx.x; e < left; e += 4 * kThreads) {
+        if (e + 4 <= left) {
+          c4[e / 4] = op4(op, a4[e / 4], b4[e / 4]);
+        } else {
+          for (uint64_t k = e0 + e; k < d.n; ++k) d.c[k] = op(d.a[k], d.b[k]);
+        }
+      }
     }
   }
 }
@@ -95,178 +100,152 @@ __global__ __launch_bounds__(kThreads) void vec_group_kernel(VecGroup g) {
 //   d1 = (ln(S/K) + (r + sigma^2/2) T) / (sigma sqrt T),  d2 = d1 - sigma sqrt T
 //   call = S N(d1) - K e^{-rT} N(d2),  put = K e^{-rT} (1 - N(d2)) - S (1 - N(d1))
 
-__device__ __forceinline__ float norm_cdf_as(float x) {
-  constexpr float p = 0.2316419f;
-  constexpr float b1 = 0.319381530f, b2 = -0.356563782f, b3 = 1.781477937f, b4 = -1.821255978f,
-                  b5 = 1.330274429f;
-  constexpr float inv_sqrt_2pi = 0.39894228040143267794f;
-  const float ax = fabsf(x);
-  const float t = __frcp_rn(fmaf(p, ax, 1.0f));
-  const float poly = t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, b5, b4), b3), b2), b1);
-  const float phi = inv_sqrt_2pi * __expf(-0.5f * ax * ax);
-  const float upper = phi * poly;          // 1 - N(|x|)
-  return x >= 0.0f ? 1.0f - upper : upper;
+// Quotients and reciprocals: a hardware reciprocal with one Newton step and,
+// for a quotient, one step on its remainder (within an ulp; the correctly
+// rounded divide takes ten instructions and was 40 of the 102 per option).
+__device__ __forceinline__ float recip(float a) {
+  const float y = __builtin_amdgcn_rcpf(a);
+  return fmaf(fmaf(-a, y, 1.0f), y, y);
+}
+__device__ __forceinline__ float refine(float q, float a, float b, float inv_b) {  // q near a / b
+  return fmaf(fmaf(-q, b, a), inv_b, q);
 }
 
-__device__ __forceinline__ void bs_price(float S, float K, float T, float r, float v, float half_v2,
-                                         float& call, float& put) {
+// N(x) and 1 - N(x).  The clamp keeps the Newton step of t finite for an
+// infinite x; a NaN comes through the exponential.
+__device__ __forceinline__ void norm_cdf_as(float x, float& n, float& m) {
+  constexpr float p = 0.2316419f;
+  constexpr float kPhi = 0.39894228040143267794f;   // 1 / sqrt(2 pi)
+  constexpr float b1 = 0.319381530f * kPhi, b2 = -0.356563782f * kPhi, b3 = 1.781477937f * kPhi,
+                  b4 = -1.821255978f * kPhi, b5 = 1.330274429f * kPhi;
+  constexpr float kHalfLog2e = -0.72134752044448170368f;   // -log2(e) / 2
+  const float ax = fabsf(x);
+  const float t = recip(fminf(fmaf(p, ax, 1.0f), 0x1p100f));
+  const float poly = t * fmaf(t, fmaf(t, fmaf(t, fmaf(t, b5, b4), b3), b2), b1);
+  const float upper = __builtin_amdgcn_exp2f(ax * ax * kHalfLog2e) * poly;   // 1 - N(|x|)
+  const float lower = 1.0f - upper;
+  n = x >= 0.0f ? lower : upper;
+  m = x >= 0.0f ? upper : lower;
+}
+
+// Uniform parameters of a launch.  Volatilities outside the range where
+// 1 / v refines a quotient take the library's divide.
+struct BsParams {
+  float r, v, inv_v, half_v2;
+};
+__device__ __forceinline__ bool plain_range(float x) { return fabsf(x) >= 0x1p-100f && fabsf(x) <= 0x1p100f; }
+
+template <bool SAFE>
+__device__ __forceinline__ void bs_price(float S, float K, float T, const BsParams& c, float& call, float& put) {
+  float ratio;
+  if constexpr (SAFE) {
+    ratio = S / K;
+  } else {
+    const float inv_k = recip(K);
+    ratio = refine(S * inv_k, S, K, inv_k);
+  }
   const float rs = __frsqrt_rn(T);
   const float sqrt_t = T * rs;
-  const float vs = v * sqrt_t;
-  const float d1 = (__logf(__fdividef(S, K)) + (r + half_v2) * T) * __fdividef(rs, v);
+  const float vs = c.v * sqrt_t;
+  const float per_vol = SAFE ? rs / c.v : refine(rs * c.inv_v, rs, c.v, c.inv_v);
+  const float d1 = (__logf(ratio) + (c.r + c.half_v2) * T) * per_vol;
   const float d2 = d1 - vs;
-  const float kd = K * __expf(-r * T);
-  const float n1 = norm_cdf_as(d1);
-  const float n2 = norm_cdf_as(d2);
+  const float kd = K * __expf(-c.r * T);
+  float n1, m1, n2, m2;
+  norm_cdf_as(d1, n1, m1);
+  norm_cdf_as(d2, n2, m2);
   call = S * n1 - kd * n2;
-  put = kd * (1.0f - n2) - S * (1.0f - n1);
+  put = kd * m2 - S * m1;
 }
 
-// Registers of one work unit: V4 float4 per thread of each input stream
-// (V4 * 1024 options per unit of 256 threads).
-template <int V4>
-struct BsUnitRegs {
-  f32x4 s[V4], k[V4], t[V4];
-};
+// One option; an operand that a bare reciprocal does not serve (strikes of
+// extreme magnitude, infinities) is priced again with the library's divide,
+// whatever its neighbours are, so an option's bits depend on itself alone.
+template <bool SAFE>
+__device__ __forceinline__ bool bs_extreme(float S, float K) {
+  return !SAFE && !(plain_range(K) && fabsf(S) <= 0x1p100f);
+}
 
-// Locate unit u and, when it is full and its streams are 16-byte aligned,
-// issue its loads; a ragged or unaligned unit returns false and is left to
-// the element-wise path.
-template <int V4, bool NT>
-__device__ __forceinline__ bool bs_load(const BsGroup& g, uint64_t u, int& q, uint64_t& e0, BsUnitRegs<V4>& x) {
-  constexpr uint64_t kUnit = V4 * 4 * kThreads;
-  q = find_request(g, u);
-  const BsDesc& d = g.d[q];
-  e0 = (u - d.unit_begin) * kUnit;
-  const uint64_t e1 = min(e0 + kUnit, d.n);
-  const bool aligned = ((reinterpret_cast<uintptr_t>(d.S) | reinterpret_cast<uintptr_t>(d.K) |
-                         reinterpret_cast<uintptr_t>(d.T) | reinterpret_cast<uintptr_t>(d.call) |
-                         reinterpret_cast<uintptr_t>(d.put)) & 15) == 0;
-  if (!aligned || e1 - e0 != kUnit) return false;
-  const f32x4* S4 = reinterpret_cast<const f32x4*>(d.S + e0);
-  const f32x4* K4 = reinterpret_cast<const f32x4*>(d.K + e0);
-  const f32x4* T4 = reinterpret_cast<const f32x4*>(d.T + e0);
+template <bool SAFE, int V4, bool NT>
+__device__ __forceinline__ void bs_quads(const BsDesc& d, uint64_t e, const BsParams& c) {
+  const f32x4u* S4 = reinterpret_cast<const f32x4u*>(d.S + e);
+  const f32x4u* K4 = reinterpret_cast<const f32x4u*>(d.K + e);
+  const f32x4u* T4 = reinterpret_cast<const f32x4u*>(d.T + e);
+  f32x4 S[V4], K[V4], T[V4];
 #pragma unroll
   for (int j = 0; j < V4; ++j) {
-    x.s[j] = stream_load<f32x4, NT>(S4 + threadIdx.x + j * kThreads);
-    x.k[j] = stream_load<f32x4, NT>(K4 + threadIdx.x + j * kThreads);
-    x.t[j] = stream_load<f32x4, NT>(T4 + threadIdx.x + j * kThreads);
+    S[j] = stream_load<f32x4u, NT>(S4 + j * kThreads);
+    K[j] = stream_load<f32x4u, NT>(K4 + j * kThreads);
+    T[j] = stream_load<f32x4u, NT>(T4 + j * kThreads);
   }
-  return true;
-}
-
-template <int V4, bool NT>
-__device__ __forceinline__ void bs_price_store(const BsDesc& d, uint64_t e0, const BsUnitRegs<V4>& x, float r,
-                                               float v, float half_v2) {
-  f32x4* C4 = reinterpret_cast<f32x4*>(d.call + e0);
-  f32x4* P4 = reinterpret_cast<f32x4*>(d.put + e0);
 #pragma unroll
   for (int j = 0; j < V4; ++j) {
-    float c0, c1, c2, c3, p0, p1, p2, p3;
-    bs_price(x.s[j].x, x.k[j].x, x.t[j].x, r, v, half_v2, c0, p0);
-    bs_price(x.s[j].y, x.k[j].y, x.t[j].y, r, v, half_v2, c1, p1);
-    bs_price(x.s[j].z, x.k[j].z, x.t[j].z, r, v, half_v2, c2, p2);
-    bs_price(x.s[j].w, x.k[j].w, x.t[j].w, r, v, half_v2, c3, p3);
-    const f32x4 c = {c0, c1, c2, c3};
-    const f32x4 p = {p0, p1, p2, p3};
-    stream_store<f32x4, NT>(c, C4 + threadIdx.x + j * kThreads);
-    stream_store<f32x4, NT>(p, P4 + threadIdx.x + j * kThreads);
+    f32x4 call, put;
+    bool extreme = false;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float x, y;
+      bs_price<SAFE>(S[j][k], K[j][k], T[j][k], c, x, y);
+      call[k] = x;
+      put[k] = y;
+      extreme |= bs_extreme<SAFE>(S[j][k], K[j][k]);
+    }
+    if (__builtin_expect(extreme, 0)) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        if (bs_extreme<SAFE>(S[j][k], K[j][k])) {
+          float x, y;
+          bs_price<true>(S[j][k], K[j][k], T[j][k], c, x, y);
+          call[k] = x;
+          put[k] = y;
+        }
+    }
+    stream_store<f32x4u>(call, reinterpret_cast<f32x4u*>(d.call + e) + j * kThreads);
+    stream_store<f32x4u>(put, reinterpret_cast<f32x4u*>(d.put + e) + j * kThreads);
   }
 }
 
-// Ragged or unaligned unit: one option per thread and step.
-template <int V4>
-__device__ __forceinline__ void bs_unit_elementwise(const BsDesc& d, uint64_t e0, float r, float v, float half_v2) {
-  constexpr uint64_t kUnit = V4 * 4 * kThreads;
-  const uint64_t e1 = min(e0 + kUnit, d.n);
-  for (uint64_t e = e0 + threadIdx.x; e < e1; e += kThreads) {
-    float c, p;
-    bs_price(d.S[e], d.K[e], d.T[e], r, v, half_v2, c, p);
-    d.call[e] = c;
-    d.put[e] = p;
-  }
-}
-
-// V4: float4 per thread of each stream per unit.  Every option is priced by
-// the same code whatever the shape or the group.
-template <int V4, bool NT>
+// Bound by memory at millions of options: 84 MB of 4M in 13.9-14.4 us, 13.6 at
+// the 6.17 TB/s of its access mix.  17.6 us with 102 instructions per option
+// (75 now); 300001 options 8.3 us element by element in 74 units of 4096, now
+// 3.8 in units of 2048.
+template <int V4, bool NT, bool SAFE>
 __global__ __launch_bounds__(kThreads) void bs_group_kernel(BsGroup g) {
-  const float r = g.rate, v = g.volatility, half_v2 = 0.5f * g.volatility * g.volatility;
+  constexpr uint64_t kUnit = V4 * 4 * kThreads;
+  const BsParams c{g.rate, g.volatility, 1.0f / g.volatility, 0.5f * g.volatility * g.volatility};
   for (uint64_t u = blockIdx.x; u < g.total_units; u += gridDim.x) {
-    int q;
-    uint64_t e0;
-    BsUnitRegs<V4> x;
-    if (bs_load<V4, NT>(g, u, q, e0, x)) bs_price_store<V4, NT>(g.d[q], e0, x, r, v, half_v2);
-    else bs_unit_elementwise<V4>(g.d[q], e0, r, v, half_v2);
+    const BsDesc& d = g.d[find_request(g, u)];
+    const uint64_t e0 = (u - d.unit_begin) * kUnit;
+    const uint64_t left = d.n - e0;
+    if (left >= kUnit) {
+      bs_quads<SAFE, V4, NT>(d, e0 + 4 * threadIdx.x, c);
+    } else {
+      for (uint64_t e = 4 * threadIdx.x; e < left; e += 4 * kThreads) {
+        if (e + 4 <= left) {
+          bs_quads<SAFE, 1, NT>(d, e0 + e, c);
+        } else {
+          for (uint64_t k = e0 + e; k < d.n; ++k) {
+            float x, y;
+            if (bs_extreme<SAFE>(d.S[k], d.K[k])) bs_price<true>(d.S[k], d.K[k], d.T[k], c, x, y);
+            else bs_price<SAFE>(d.S[k], d.K[k], d.T[k], c, x, y);
+            d.call[k] = x;
+            d.put[k] = y;
+          }
+        }
+      }
+    }
   }
 }
 
 }  // namespace
 
-void finalize_vec_group(VecGroup& g) {
-  uint64_t u = 0;
-  for (uint32_t i = 0; i < g.count; ++i) {
-    g.d[i].unit_begin = u;
-    u += (g.d[i].n + kVecUnit - 1) / kVecUnit;
-  }
-  g.total_units = u;
-}
+namespace {
 
-void finalize_bs_group(BsGroup& g) {
-  uint64_t u = 0;
-  for (uint32_t i = 0; i < g.count; ++i) {
-    g.d[i].unit_begin = u;
-    u += (g.d[i].n + kBsUnit - 1) / kBsUnit;
-  }
-  g.total_units = u;
-}
+constexpr uint64_t kMaxGrid = 1ull << 24;
 
-// Tuning overrides (read once per process): GVM_STREAM_GRID replaces the
-// grid, GVM_STREAM_NT = 0 / 1 forces cached / non-temporal access.
-int stream_grid(int grid_cap, int dflt) {
-  static const int env = [] {
-    const char* e = getenv("GVM_STREAM_GRID");
-    return e ? atoi(e) : 0;
-  }();
-  if (grid_cap > 0) return grid_cap;
-  return env > 0 ? env : dflt;
-}
-
-bool stream_nt(uint64_t group_bytes) {
-  static const int env = [] {
-    const char* e = getenv("GVM_STREAM_NT");
-    return e ? atoi(e) : -1;
-  }();
-  return env >= 0 ? env != 0 : group_bytes > kMallBytes;
-}
-
-template <class Op>
-hipError_t launch_vec(const VecGroup& g, hipStream_t s, int grid_cap) {
-  const int grid = static_cast<int>(std::min<uint64_t>(g.total_units, static_cast<uint64_t>(stream_grid(grid_cap, kVecGrid))));
-  const uint64_t bytes = g.total_units * kVecUnit * 12;
-  return stream_nt(bytes) ? launch_group(vec_group_kernel<Op, true>, grid, kThreads, s, g)
-                          : launch_group(vec_group_kernel<Op, false>, grid, kThreads, s, g);
-}
-
-hipError_t launch_vecadd_group(const VecGroup& g, hipStream_t s, int grid_cap) { return launch_vec<AddOp>(g, s, grid_cap); }
-
-hipError_t launch_vecmul_group(const VecGroup& g, hipStream_t s, int grid_cap) { return launch_vec<MulOp>(g, s, grid_cap); }
-
-// Black-Scholes launch shape: float4 per thread per stream (GVM_BS_V4 = 2, 4
-// or 8), read once per process.
-int bs_v4() {
-  static const int v4 = [] {
-    const char* e = getenv("GVM_BS_V4");
-    const int x = e ? atoi(e) : kBsV4;
-    return (x == 2 || x == 8) ? x : 4;
-  }();
-  return v4;
-}
-
-template <int V4>
-hipError_t launch_bs_shape(const BsGroup& g0, hipStream_t s, int grid_cap) {
-  // the unit size of the shape: recount the units of a copy of the group
-  BsGroup g = g0;
+// Cut the requests of a launch into units of V4 float4 per thread.
+template <int V4, class G>
+int cut_units(G& g) {
   constexpr uint64_t kUnit = V4 * 4 * kThreads;
   uint64_t u = 0;
   for (uint32_t i = 0; i < g.count; ++i) {
@@ -274,17 +253,45 @@ hipError_t launch_bs_shape(const BsGroup& g0, hipStream_t s, int grid_cap) {
     u += (g.d[i].n + kUnit - 1) / kUnit;
   }
   g.total_units = u;
-  const int grid = static_cast<int>(std::min<uint64_t>(g.total_units, static_cast<uint64_t>(stream_grid(grid_cap, kBsGrid))));
-  return stream_nt(g.total_units * kUnit * 20) ? launch_group(bs_group_kernel<V4, true>, grid, kThreads, s, g)
-                                               : launch_group(bs_group_kernel<V4, false>, grid, kThreads, s, g);
+  return static_cast<int>(std::min(u, kMaxGrid));
 }
 
-hipError_t launch_bs_group(const BsGroup& g, hipStream_t s, int grid_cap) {
-  switch (bs_v4()) {
-    case 2: return launch_bs_shape<2>(g, s, grid_cap);
-    case 8: return launch_bs_shape<8>(g, s, grid_cap);
-    default: return launch_bs_shape<4>(g, s, grid_cap);
-  }
+// Whether a launch's inputs are loaded non-temporal.  Tuning override (read
+// once per process): GVM_STREAM_NT = 0 / 1.
+template <class G>
+bool stream_nt(const G& g, uint64_t bytes_per_element) {
+  static const int env = [] {
+    const char* e = getenv("GVM_STREAM_NT");
+    return e ? atoi(e) : -1;
+  }();
+  if (env >= 0) return env != 0;
+  uint64_t n = 0;
+  for (uint32_t i = 0; i < g.count; ++i) n += g.d[i].n;
+  return n > kCachedInput / bytes_per_element;
+}
+
+template <class Op>
+hipError_t launch_vec(const VecGroup& g0, hipStream_t s) {
+  VecGroup g = g0;
+  if (stream_nt(g, 8)) return launch_group(vec_group_kernel<Op, 4, true>, cut_units<4>(g), kThreads, s, g);
+  return launch_group(vec_group_kernel<Op, 2, false>, cut_units<2>(g), kThreads, s, g);
+}
+
+}  // namespace
+
+hipError_t launch_vecadd_group(const VecGroup& g, hipStream_t s) { return launch_vec<AddOp>(g, s); }
+
+hipError_t launch_vecmul_group(const VecGroup& g, hipStream_t s) { return launch_vec<MulOp>(g, s); }
+
+hipError_t launch_bs_group(const BsGroup& g0, hipStream_t s) {
+  BsGroup g = g0;
+  // 1 / sigma refines a quotient in this range; outside it (zero, NaN) the
+  // kernel with the library's divide runs
+  const float v = std::fabs(g.volatility);
+  if (!(v >= 0x1p-60f && v <= 0x1p60f))
+    return launch_group(bs_group_kernel<2, false, true>, cut_units<2>(g), kThreads, s, g);
+  if (stream_nt(g, 12)) return launch_group(bs_group_kernel<4, true, false>, cut_units<4>(g), kThreads, s, g);
+  return launch_group(bs_group_kernel<2, false, false>, cut_units<2>(g), kThreads, s, g);
 }
 
 }  // namespace gvm
