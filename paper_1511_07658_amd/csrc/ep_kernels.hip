@@ -23,7 +23,7 @@ namespace {
 
 constexpr int kEpThreads = 512;
 constexpr int kEpWaves = kEpThreads / 64;
-constexpr int kEpGrid = 1 << 20;   // workgroups of the unit launch: one per unit up to here
+constexpr uint64_t kEpGrid = 1 << 20;   // workgroups of the unit launch: one per unit up to here
 static_assert(kEpUnit / kEpThreads <= 255, "per-thread 8-bit annulus counts of a unit would overflow");
 static_assert(kEpUnit <= 65535 && kEpRecordBytes >= 2 * 8 + 10 * 2, "a record holds 16-bit annulus counts");
 
@@ -191,12 +191,13 @@ static_assert(sizeof(EpRecord) == kEpRecordBytes, "record layout");
 // and 32-bit multiplies included.  8 waves per workgroup on small units fill
 // the SIMDs for requests of any size (a unit of 2^15 pairs on 256 threads left
 // a request of 2^15 pairs to one CU: 88 us).
-__global__ __launch_bounds__(kEpThreads) void ep_units_kernel(EpGroup g) {
+template <int N>
+__global__ __launch_bounds__(kEpThreads) void ep_units_kernel(EpGroupN<N> g) {
   __shared__ LogEntry table[kLogTable];
   __shared__ double wsx[kEpWaves], wsy[kEpWaves];
   __shared__ uint64_t wq[kEpWaves][3];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (uint64_t u = blockIdx.x; u < g.total_units; u += gridDim.x) {
+  for (uint64_t u = blockIdx.x; u < g.total_units; u += g.grid) {
     const int r = find_request(g, u);
     const EpDesc& d = g.d[r];
     const uint64_t local = u - d.unit_begin;
@@ -266,7 +267,8 @@ __global__ __launch_bounds__(kEpThreads) void ep_units_kernel(EpGroup g) {
 // for 32 records and 13 us for 1024).
 constexpr int kEpSumThreads = 512;
 
-__global__ __launch_bounds__(kEpSumThreads) void ep_reduce_kernel(EpGroup g) {
+template <int N>
+__global__ __launch_bounds__(kEpSumThreads) void ep_reduce_kernel(EpGroupN<N> g) {
   constexpr int kWaves = kEpSumThreads / 64;
   __shared__ double ws[kWaves][2];
   __shared__ uint64_t wq[kWaves][10];
@@ -322,11 +324,21 @@ void finalize_ep_group(EpGroup& g) {
   g.total_units = u;
 }
 
-hipError_t launch_ep_group(const EpGroup& g, hipStream_t s) {
-  const int grid = static_cast<int>(std::min<uint64_t>(g.total_units, kEpGrid));
-  const hipError_t e = launch_group(ep_units_kernel, grid, kEpThreads, s, g);
+namespace {
+template <int N>
+hipError_t launch_ep(const EpGroupN<N>& g, hipStream_t s) {
+  const hipError_t e = launch_group(ep_units_kernel<N>, g.grid, kEpThreads, s, g);
   if (e != hipSuccess || g.total_units == g.count) return e;
-  return launch_group(ep_reduce_kernel, static_cast<int>(g.count), kEpSumThreads, s, g);
+  return launch_group(ep_reduce_kernel<N>, g.count, kEpSumThreads, s, g);
+}
+}  // namespace
+
+hipError_t launch_ep_group(const EpGroup& g0, hipStream_t s) {
+  const uint32_t grid = static_cast<uint32_t>(std::min(g0.total_units, kEpGrid));
+  if (g0.count == 1) return launch_ep(EpGroupN<1>{1, grid, g0.total_units, {g0.d[0]}}, s);
+  EpGroup g = g0;
+  g.grid = grid;
+  return launch_ep(g, s);
 }
 
 }  // namespace gvm

@@ -15,6 +15,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 // unit_begin <= u (descriptors are in unit order, the first starts at 0).
 template <class G>
 __device__ __forceinline__ int find_request(const G& g, uint64_t u) {
+  if constexpr (sizeof(g.d) == sizeof(g.d[0])) return 0;
   int lo = 0, hi = static_cast<int>(g.count) - 1;
   while (lo < hi) {
     int mid = (lo + hi + 1) >> 1;
@@ -23,7 +24,8 @@ __device__ __forceinline__ int find_request(const G& g, uint64_t u) {
   return lo;
 }
 
-// Launch `kernel(g)` on `s` (nothing for an empty grid).
+// Launch `kernel(g)` on `s` (nothing for an empty grid).  Kernels take the grid
+// from the group: reading gridDim would add the hidden arguments (256 bytes).
 template <class G>
 hipError_t launch_group(void (*kernel)(G), int grid, int block, hipStream_t s, const G& g) {
   if (grid <= 0) return hipSuccess;

@@ -12,7 +12,11 @@
 
 namespace gvm {
 
-constexpr int kMaxGroup = 32;  // requests per grouped launch (kernel-argument capacity, < 2 KiB)
+// Requests per grouped launch.  The descriptors are kernel arguments, and a
+// launch costs the host by their size (2.7 us with 64 bytes, 3.3 with 256, 4.1
+// with 1408), so each group type comes with a capacity N: kMaxGroup (< 2 KiB)
+// for a group, 1 for a launch of one request.
+constexpr int kMaxGroup = 32;
 
 struct VecDesc {
   const float* a;
@@ -22,12 +26,14 @@ struct VecDesc {
   uint64_t unit_begin;  // first work unit of this request in the group
 };
 
-struct VecGroup {
+template <int N>
+struct VecGroupN {
   uint32_t count;
-  uint32_t pad;
+  uint32_t grid;         // workgroups of the launch
   uint64_t total_units;
-  VecDesc d[kMaxGroup];
+  VecDesc d[N];
 };
+using VecGroup = VecGroupN<kMaxGroup>;
 
 struct BsDesc {
   const float* S;
@@ -39,14 +45,16 @@ struct BsDesc {
   uint64_t unit_begin;
 };
 
-struct BsGroup {
+template <int N>
+struct BsGroupN {
   uint32_t count;
-  uint32_t pad;
+  uint32_t grid;
   uint64_t total_units;
   float rate;
   float volatility;
-  BsDesc d[kMaxGroup];
+  BsDesc d[N];
 };
+using BsGroup = BsGroupN<kMaxGroup>;
 
 struct GemmDesc {
   const float* A;
@@ -60,19 +68,21 @@ struct GemmDesc {
 
 constexpr int kGroupXcds = 8;  // MI355X: workgroup w is dispatched to XCD w % 8
 
-struct GemmGroup {
+template <int N>
+struct GemmGroupN {
   uint32_t count;
   uint32_t total_units;
-  GemmDesc d[kMaxGroup];
+  uint32_t grid;
+  uint32_t balanced;
+  GemmDesc d[N];
   // Balanced launch (mixed sizes, one workgroup per tile): the units are cut
   // into 16 slices of equal k-step work, slice s = [cut[s], cut[s + 1]), and
   // each XCD takes two of them (csrc/gemm_balance.hpp): balanced = 1 two
   // neighbouring slices, balanced = 2 one from each end.  Filled by
-  // finalize_gemm_group; set by the launcher.
-  uint32_t cut[2 * kGroupXcds + 1];
-  uint32_t balanced;
-  uint32_t pad[2];
+  // finalize_gemm_group; set by the launcher.  One request is never mixed.
+  uint32_t cut[N > 1 ? 2 * kGroupXcds + 1 : 1];
 };
+using GemmGroup = GemmGroupN<kMaxGroup>;
 
 struct EpDesc {
   const uint64_t* key;   // (k0, k1)
@@ -84,12 +94,14 @@ struct EpDesc {
   uint64_t units;
 };
 
-struct EpGroup {
+template <int N>
+struct EpGroupN {
   uint32_t count;
-  uint32_t pad;
+  uint32_t grid;
   uint64_t total_units;
-  EpDesc d[kMaxGroup];
+  EpDesc d[N];
 };
+using EpGroup = EpGroupN<kMaxGroup>;
 
 // SGEMM tile configurations available to the tuner.  Every configuration sums
 // a C element in the same order, so the choice changes a launch's time and

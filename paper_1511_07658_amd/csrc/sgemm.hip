@@ -127,11 +127,8 @@ __device__ __forceinline__ f32x4 inside4(f32x4 x, int n, int r, int c) {
 // slice x from the long end and then slice 15 - x from the short end, so every
 // XCD ends on short tiles; the grid holds as many workgroups per XCD as the
 // longest pair has units (the rest exit at once).
-//
-// `first` is the group's first descriptor again: a launch of one request reads
-// it together with the count instead of after the search.
-template <int BM, int BN, int BK, int WM, int WN, int MF, int DEPTH, bool PIPE>
-__global__ __launch_bounds__(WM * WN * 64) void sgemm_group_kernel(GemmDesc first, GemmGroup g) {
+template <int BM, int BN, int BK, int WM, int WN, int MF, int DEPTH, bool PIPE, int N>
+__global__ __launch_bounds__(WM * WN * 64) void sgemm_group_kernel(GemmGroupN<N> g) {
   constexpr int NT = WM * WN * 64;
   constexpr int TM = BM / WM, TN = BN / WN;
   constexpr int FM = TM / MF, FN = TN / MF;
@@ -156,9 +153,9 @@ __global__ __launch_bounds__(WM * WN * 64) void sgemm_group_kernel(GemmDesc firs
   const int li = lane % MF, lg = lane / MF;
 
   // the workgroup's unit (tile)
-  uint32_t u = (blockIdx.x % kXcds) * (gridDim.x / kXcds) + blockIdx.x / kXcds;
+  uint32_t u = (blockIdx.x % kXcds) * (g.grid / kXcds) + blockIdx.x / kXcds;
   uint32_t uend = g.total_units;
-  if (g.balanced) {
+  if (N > 1 && g.balanced) {
     // the j-th workgroup of XCD x takes the j-th unit of the XCD's two
     // slices; the grid holds as many per XCD as the longest pair has units
     // (the slices of xcd_slices(): 2x and 2x + 1, or x and 15 - x when paired)
@@ -171,8 +168,7 @@ __global__ __launch_bounds__(WM * WN * 64) void sgemm_group_kernel(GemmDesc firs
     uend = j < len0 ? g.cut[s0 + 1] : g.cut[s1 + 1];
   }
   if (u >= uend) return;
-  GemmDesc d = first;
-  if (g.count > 1) d = g.d[find_request(g, u)];
+  const GemmDesc& d = g.d[find_request(g, u)];
   const int n = static_cast<int>(d.n);
   const uint32_t local = u - d.unit_begin;
   const int row0 = static_cast<int>(local / d.tiles_n) * BM;
@@ -450,22 +446,26 @@ constexpr uint64_t kTileTableEnd = 1ull << 30;  // the last row's bound: every l
 // BT (B staged transposed in LDS) is false in every configuration: the 16-byte
 // fragment reads it gives B cost four times the fetch or LDS write instructions.
 template <int BM, int BN, int BK, int WM, int WN, bool BT, int MF, int DEPTH, bool PIPE>
-hipError_t launch_cfg(const GemmGroup& g, hipStream_t s) {
+hipError_t launch_cfg(const GemmGroup& g0, hipStream_t s) {
   constexpr int NT = WM * WN * 64;
   // one workgroup per unit, in whole rounds over the 8 XCDs
-  uint32_t per_xcd = (g.total_units + kXcds - 1) / kXcds;
-  if (g.balanced) {  // as many as the longest XCD pair of slices has units
+  uint32_t per_xcd = (g0.total_units + kXcds - 1) / kXcds;
+  if (g0.balanced) {  // as many as the longest XCD pair of slices has units
     per_xcd = 0;
     for (int x = 0; x < kXcds; ++x) {
       int s0, s1;
-      xcd_slices(x, g.balanced == 2, &s0, &s1);
-      per_xcd = std::max(per_xcd, (g.cut[s0 + 1] - g.cut[s0]) + (g.cut[s1 + 1] - g.cut[s1]));
+      xcd_slices(x, g0.balanced == 2, &s0, &s1);
+      per_xcd = std::max(per_xcd, (g0.cut[s0 + 1] - g0.cut[s0]) + (g0.cut[s1 + 1] - g0.cut[s1]));
     }
   }
-  if (per_xcd == 0) return hipSuccess;
-  void (*const kernel)(GemmDesc, GemmGroup) = sgemm_group_kernel<BM, BN, BK, WM, WN, MF, DEPTH, PIPE>;
-  void* args[] = {const_cast<GemmDesc*>(&g.d[0]), const_cast<GemmGroup*>(&g)};
-  return hipLaunchKernel(reinterpret_cast<const void*>(kernel), dim3(per_xcd * kXcds), dim3(NT), args, 0, s);
+  const uint32_t grid = per_xcd * kXcds;
+  if (g0.count == 1) {
+    const GemmGroupN<1> g{1, g0.total_units, grid, 0, {g0.d[0]}, {0}};
+    return launch_group(sgemm_group_kernel<BM, BN, BK, WM, WN, MF, DEPTH, PIPE, 1>, grid, NT, s, g);
+  }
+  GemmGroup g = g0;
+  g.grid = grid;
+  return launch_group(sgemm_group_kernel<BM, BN, BK, WM, WN, MF, DEPTH, PIPE, kMaxGroup>, grid, NT, s, g);
 }
 
 }  // namespace

@@ -57,11 +57,11 @@ __device__ __forceinline__ f32x4 op4(Op op, f32x4 a, f32x4 b) {
 // Bound by memory.  The operands of a request of odd length start anywhere
 // (b is a + n), so every access is 16 bytes at float alignment: 14.5M elements
 // 27.6 us (6.3 TB/s, as 2^24 has), 34.8 element by element.
-template <class Op, int V4, bool NT>
-__global__ __launch_bounds__(kThreads) void vec_group_kernel(VecGroup g) {
+template <class Op, int V4, bool NT, int N>
+__global__ __launch_bounds__(kThreads) void vec_group_kernel(VecGroupN<N> g) {
   constexpr uint64_t kUnit = V4 * 4 * kThreads;
   Op op;
-  for (uint64_t u = blockIdx.x; u < g.total_units; u += gridDim.x) {
+  for (uint64_t u = blockIdx.x; u < g.total_units; u += g.grid) {
     const VecDesc& d = g.d[find_request(g, u)];
     const uint64_t e0 = (u - d.unit_begin) * kUnit;
     const uint64_t left = d.n - e0;
@@ -209,11 +209,11 @@ __device__ __forceinline__ void bs_quads(const BsDesc& d, uint64_t e, const BsPa
 // the 6.17 TB/s of its access mix.  17.6 us with 102 instructions per option
 // (75 now); 300001 options 8.3 us element by element in 74 units of 4096, now
 // 3.8 in units of 2048.
-template <int V4, bool NT, bool SAFE>
-__global__ __launch_bounds__(kThreads) void bs_group_kernel(BsGroup g) {
+template <int V4, bool NT, bool SAFE, int N>
+__global__ __launch_bounds__(kThreads) void bs_group_kernel(BsGroupN<N> g) {
   constexpr uint64_t kUnit = V4 * 4 * kThreads;
   const BsParams c{g.rate, g.volatility, 1.0f / g.volatility, 0.5f * g.volatility * g.volatility};
-  for (uint64_t u = blockIdx.x; u < g.total_units; u += gridDim.x) {
+  for (uint64_t u = blockIdx.x; u < g.total_units; u += g.grid) {
     const BsDesc& d = g.d[find_request(g, u)];
     const uint64_t e0 = (u - d.unit_begin) * kUnit;
     const uint64_t left = d.n - e0;
@@ -245,7 +245,7 @@ constexpr uint64_t kMaxGrid = 1ull << 24;
 
 // Cut the requests of a launch into units of V4 float4 per thread.
 template <int V4, class G>
-int cut_units(G& g) {
+void cut_units(G& g) {
   constexpr uint64_t kUnit = V4 * 4 * kThreads;
   uint64_t u = 0;
   for (uint32_t i = 0; i < g.count; ++i) {
@@ -253,7 +253,7 @@ int cut_units(G& g) {
     u += (g.d[i].n + kUnit - 1) / kUnit;
   }
   g.total_units = u;
-  return static_cast<int>(std::min(u, kMaxGrid));
+  g.grid = static_cast<uint32_t>(std::min(u, kMaxGrid));
 }
 
 // Whether a launch's inputs are loaded non-temporal.  Tuning override (read
@@ -270,11 +270,33 @@ bool stream_nt(const G& g, uint64_t bytes_per_element) {
   return n > kCachedInput / bytes_per_element;
 }
 
-template <class Op>
-hipError_t launch_vec(const VecGroup& g0, hipStream_t s) {
+template <class Op, int V4, bool NT>
+hipError_t launch_vec_shape(const VecGroup& g0, hipStream_t s) {
+  if (g0.count == 1) {
+    VecGroupN<1> g{1, 0, 0, {g0.d[0]}};
+    cut_units<V4>(g);
+    return launch_group(vec_group_kernel<Op, V4, NT, 1>, g.grid, kThreads, s, g);
+  }
   VecGroup g = g0;
-  if (stream_nt(g, 8)) return launch_group(vec_group_kernel<Op, 4, true>, cut_units<4>(g), kThreads, s, g);
-  return launch_group(vec_group_kernel<Op, 2, false>, cut_units<2>(g), kThreads, s, g);
+  cut_units<V4>(g);
+  return launch_group(vec_group_kernel<Op, V4, NT, kMaxGroup>, g.grid, kThreads, s, g);
+}
+
+template <class Op>
+hipError_t launch_vec(const VecGroup& g, hipStream_t s) {
+  return stream_nt(g, 8) ? launch_vec_shape<Op, 4, true>(g, s) : launch_vec_shape<Op, 2, false>(g, s);
+}
+
+template <int V4, bool NT, bool SAFE>
+hipError_t launch_bs_shape(const BsGroup& g0, hipStream_t s) {
+  if (g0.count == 1) {
+    BsGroupN<1> g{1, 0, 0, g0.rate, g0.volatility, {g0.d[0]}};
+    cut_units<V4>(g);
+    return launch_group(bs_group_kernel<V4, NT, SAFE, 1>, g.grid, kThreads, s, g);
+  }
+  BsGroup g = g0;
+  cut_units<V4>(g);
+  return launch_group(bs_group_kernel<V4, NT, SAFE, kMaxGroup>, g.grid, kThreads, s, g);
 }
 
 }  // namespace
@@ -283,15 +305,12 @@ hipError_t launch_vecadd_group(const VecGroup& g, hipStream_t s) { return launch
 
 hipError_t launch_vecmul_group(const VecGroup& g, hipStream_t s) { return launch_vec<MulOp>(g, s); }
 
-hipError_t launch_bs_group(const BsGroup& g0, hipStream_t s) {
-  BsGroup g = g0;
+hipError_t launch_bs_group(const BsGroup& g, hipStream_t s) {
   // 1 / sigma refines a quotient in this range; outside it (zero, NaN) the
   // kernel with the library's divide runs
   const float v = std::fabs(g.volatility);
-  if (!(v >= 0x1p-60f && v <= 0x1p60f))
-    return launch_group(bs_group_kernel<2, false, true>, cut_units<2>(g), kThreads, s, g);
-  if (stream_nt(g, 12)) return launch_group(bs_group_kernel<4, true, false>, cut_units<4>(g), kThreads, s, g);
-  return launch_group(bs_group_kernel<2, false, false>, cut_units<2>(g), kThreads, s, g);
+  if (!(v >= 0x1p-60f && v <= 0x1p60f)) return launch_bs_shape<2, false, true>(g, s);
+  return stream_nt(g, 12) ? launch_bs_shape<4, true, false>(g, s) : launch_bs_shape<2, false, false>(g, s);
 }
 
 }  // namespace gvm
