@@ -23,7 +23,8 @@ class CopyEngine {
   // Queue a copy of `bytes` from src to dst, split into chunks that run on
   // the workers in parallel.  `pending` is incremented by the number of
   // chunks now and decremented as each chunk lands; the copy is complete
-  // when it reads 0 (acquire).  Without workers the copy runs inline.
+  // when it reads 0 (acquire).  Without workers, and for a few KiB, the copy
+  // runs inline.
   // `urgent` chunks (a small request's) go ahead of every queued ordinary
   // chunk; each of the two queues is first-in first-out.
   void submit(void* dst, const void* src, size_t bytes, std::atomic<int>* pending, bool urgent = false);

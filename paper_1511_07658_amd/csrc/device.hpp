@@ -41,6 +41,7 @@ struct Job {
   // each lands in the pinned staging, the output's pieces come back to shared
   // memory as each leaves the device.
   bool local = false;            // small copies: on the kernel's own stream, whole
+  bool inline_io = false;        // device-private: input with the launch, result straight to the staging
   bool pieces = false;
   uint32_t in_pieces = 0, in_sent = 0;                 // input pieces; those whose H2D is queued
   std::unique_ptr<std::atomic<int>[]> in_pending;      // host copy chunks in flight per input piece

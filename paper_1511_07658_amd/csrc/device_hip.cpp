@@ -267,6 +267,14 @@ class HipDevice final : public Device {
       jobs[i]->batch = b;
       jobs[i]->done_index = static_cast<int>(i);
       jobs[i]->t_launch_ns = now_ns();
+      // The EP-like kernel's 16 bytes of input come with the launch and its 96
+      // bytes of result are written to the pinned staging by the kernel (the
+      // completion event's system-scope release makes them visible): two
+      // copies per request cost more than a small tally (8 requests of 2^24
+      // pairs in one launch: 20 us before the kernels and 53 us after them).
+      // Copies stay where they are timed, and in graphs, whose arguments are
+      // fixed.
+      jobs[i]->inline_io = jobs[i]->req.kernel_id == GVM_K_EP && !cfg_.batch_timing && !cfg_.use_graphs;
       if (jobs[i]->in_done) b->sync.push_back(static_cast<hipEvent_t>(jobs[i]->in_done));  // recycled with b
       auto pre = pre_copies_.find(jobs[i]);
       if (pre != pre_copies_.end()) {
@@ -664,12 +672,12 @@ class HipDevice final : public Device {
   }
 
   int enqueue_in(Job* j, hipStream_t s) {
-    if (!j->copy_in || j->pieces) return GVM_OK;  // a piecewise input is queued as it lands
+    if (!j->copy_in || j->pieces || j->inline_io) return GVM_OK;  // a piecewise input is queued as it lands
     return timed_copy(j->slot, j->pin, j->lay.in_bytes, hipMemcpyHostToDevice, s, &static_cast<Batch*>(j->batch)->copies);
   }
 
   int enqueue_out(Job* j, hipStream_t s) {
-    if (!j->copy_out) return GVM_OK;
+    if (!j->copy_out || j->inline_io) return GVM_OK;
     const uint64_t o = slot_out_offset(j->lay);
     auto* b = static_cast<Batch*>(j->batch);
     if (!j->out_pieces)
@@ -691,10 +699,11 @@ class HipDevice final : public Device {
     return GVM_OK;
   }
 
-  // The plan's view of a job.
+  // The plan's view of a job (one with inline_io has no copies, and completes
+  // with its launch).
   static PlanJob plan_job(const Job* j) {
     const int k = static_cast<int>(j->req.kernel_id);
-    return PlanJob{k, j->req.n, j->copy_in, j->copy_out, j->local, j->pieces && j->copy_in, j->out_pieces > 0};
+    return PlanJob{k, j->req.n, j->copy_in && !j->inline_io, j->copy_out && !j->inline_io, j->local, j->pieces && j->copy_in, j->out_pieces > 0};
   }
 
   // One grouped launch per kernel id, at most kMaxGroup requests each, dealt
@@ -784,8 +793,13 @@ class HipDevice final : public Device {
       EpGroup eg{};
       eg.count = static_cast<uint32_t>(cnt);
       for (size_t i = 0; i < cnt; ++i) {
-        eg.d[i].key = reinterpret_cast<const uint64_t*>(v[i]->slot);
-        eg.d[i].out = reinterpret_cast<uint64_t*>(v[i]->slot + slot_out_offset(v[i]->lay));
+        const uint64_t out = slot_out_offset(v[i]->lay);
+        eg.d[i].key = reinterpret_cast<uint64_t*>(v[i]->slot);
+        if (v[i]->inline_io && v[i]->copy_in) {
+          eg.d[i].inline_key = 1;
+          memcpy(eg.d[i].key_value, v[i]->pin, sizeof(eg.d[i].key_value));
+        }
+        eg.d[i].out = reinterpret_cast<uint64_t*>((v[i]->inline_io && v[i]->copy_out ? v[i]->pin : v[i]->slot) + out);
         eg.d[i].partial = reinterpret_cast<uint64_t*>(v[i]->slot + slot_scratch_offset(v[i]->lay));
         eg.d[i].n = v[i]->req.n;
       }

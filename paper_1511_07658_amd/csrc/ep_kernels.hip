@@ -203,7 +203,9 @@ __global__ __launch_bounds__(kEpThreads) void ep_units_kernel(EpGroupN<N> g) {
     const uint64_t local = u - d.unit_begin;
     const uint64_t p0 = local * d.unit;                      // first pair (even)
     const uint64_t p1 = min(p0 + d.unit, d.n);               // end of pairs
-    const uint64_t k0 = d.key[0], k1 = d.key[1];
+    const uint64_t k0 = d.inline_key ? d.key_value[0] : d.key[0];
+    const uint64_t k1 = d.inline_key ? d.key_value[1] : d.key[1];
+    if (d.inline_key && local == 0 && threadIdx.x < 2) d.key[threadIdx.x] = threadIdx.x ? k1 : k0;
     if (u == blockIdx.x && threadIdx.x < kLogTable) table[threadIdx.x] = log_entry(threadIdx.x);
     uint64_t h, l;
     mul128(kPhiloxM0, k0, h, l);

@@ -85,13 +85,16 @@ struct GemmGroupN {
 using GemmGroup = GemmGroupN<kMaxGroup>;
 
 struct EpDesc {
-  const uint64_t* key;   // (k0, k1)
+  uint64_t* key;         // (k0, k1) on the device
   uint64_t* out;         // sx, sy (binary64 bit patterns), q[0..9]
   void* partial;         // one record (kEpRecordBytes) per work unit, 8-byte aligned
   uint64_t n;            // pairs
   uint64_t unit;         // pairs per work unit (ep_unit(n), set by finalize_ep_group)
   uint64_t unit_begin;
   uint64_t units;
+  // inline_key: the key comes with the launch, and the kernel leaves it at
+  // `key` for requests on the resident input
+  uint64_t inline_key, key_value[2];
 };
 
 template <int N>

@@ -63,8 +63,8 @@ extern "C" int gvm_plain_run(int kernel_id, const void* in, void* out, uint64_t 
   } else if (kernel_id == GVM_K_EP) {
     gvm::EpGroup g{};
     g.count = 1;
-    g.d[0] = gvm::EpDesc{reinterpret_cast<const uint64_t*>(dev), reinterpret_cast<uint64_t*>(fout),
-                         reinterpret_cast<uint64_t*>(dev + gvm::slot_scratch_offset(lay)), n, 0, 0};
+    g.d[0] = gvm::EpDesc{reinterpret_cast<uint64_t*>(dev), reinterpret_cast<uint64_t*>(fout),
+                         reinterpret_cast<uint64_t*>(dev + gvm::slot_scratch_offset(lay)), n};
     gvm::finalize_ep_group(g);
     e = gvm::launch_ep_group(g, nullptr);
   } else {

@@ -93,7 +93,7 @@ extern "C" int gvm_plain_run_noalloc(int kernel_id, const void* d_in, void* d_ou
   } else if (kernel_id == GVM_K_EP) {
     gvm::EpGroup g{};
     g.count = 1;
-    g.d[0] = gvm::EpDesc{static_cast<const uint64_t*>(d_in), static_cast<uint64_t*>(d_out), part, n, 0, 0};
+    g.d[0] = gvm::EpDesc{static_cast<uint64_t*>(const_cast<void*>(d_in)), static_cast<uint64_t*>(d_out), part, n};
     gvm::finalize_ep_group(g);
     e = gvm::launch_ep_group(g, s);
   } else {
