@@ -66,13 +66,13 @@ struct Batch {
 // Tile configuration of one grouped SGEMM launch, its requests sorted by
 // size from the largest down (every configuration gives the same bits, so
 // the choice is about speed alone).  A mix of sizes that gives kMixConfig's
-// tiles (64x64, k-tiles of 64) two rounds over the chip takes it: small
+// tiles (128x64 on eight waves) two rounds over the chip takes it: small
 // tiles balance the short and the long requests over the CUs (the 32-rank
-// uneven launch: 477.5 us, against 478-482 us with 128x64 and 64x128 tiles
-// and more than 492 us with 128x128).  Everything else is chosen by
-// gemm_config_for.  Tuning override for mixed sizes:
+// uneven launch: 487 us, against 489-490 us with 64x128 and 128x64 tiles of
+// four waves, 494-496 with 64x64 and 505 and more with 128x128).  Everything
+// else is chosen by gemm_config_for.  Tuning override for mixed sizes:
 // GVM_SGEMM_MIX_CONFIG=<index>.
-constexpr int kMixConfig = 10;
+constexpr int kMixConfig = 18;
 
 int gemm_group_config(const GemmGroup& g) {
   const GemmConfig& mix = gemm_config(kMixConfig);

@@ -18,24 +18,24 @@ namespace gvm {
 // and e3 are the inverse of the rate a CU reaches with one, two and more tiles
 // (one tile alone has nothing to hide its barriers and fetches behind).  t0
 // and e1 .. e3 are fitted to launches of 1, 2, 3, 4, 8 and 16 requests of 46
-// sizes from 64 to 2048 on an MI355X (rms 2-6 % per configuration).  Over
+// sizes from 64 to 2048 on an MI355X (rms 2-7 % per configuration).  Over
 // those 276 launches the cheapest configuration by this formula is on average
-// 0.5 % and at most 6.5 % slower than the fastest of all 30 measured, where
-// a table by size alone (tuned on 8 requests) is 13 % and up to 87 % slower
-// for 4 requests and 1.4 % and up to 10 % for 16.
+// 0.7 % and at most 13 % (0.5 us, n = 96) slower than the fastest of all 31
+// measured, where a table by size alone (the fastest for 8 requests) is 13 %
+// and up to 89 % slower for 4 requests and 2 % and up to 15 % for 16.
 struct GemmCost {
   int config;
   uint32_t bm, bn;
   float t0, e1, e2, e3;
 };
 constexpr GemmCost kGemmCosts[] = {
-    {0, 32, 32, 4.4f, 0.43f, 1.19f, 1.42f},    {1, 32, 32, 4.2f, 0.95f, 1.19f, 1.37f},
-    {3, 32, 64, 4.3f, 1.03f, 1.18f, 1.22f},    {5, 64, 32, 4.5f, 0.89f, 1.14f, 1.19f},
-    {6, 64, 64, 4.1f, 1.06f, 1.16f, 1.15f},    {9, 64, 64, 4.1f, 1.12f, 1.17f, 1.15f},
-    {10, 64, 64, 5.2f, 1.01f, 1.13f, 1.14f},   {11, 64, 96, 4.2f, 1.15f, 1.21f, 1.20f},
-    {13, 96, 96, 4.7f, 1.19f, 1.22f, 1.20f},   {17, 64, 128, 4.7f, 1.09f, 1.12f, 1.11f},
-    {18, 128, 64, 4.3f, 1.11f, 1.11f, 1.10f},  {22, 128, 128, 4.7f, 1.08f, 1.09f, 1.10f},
-    {24, 128, 256, 5.9f, 1.06f, 1.07f, 1.08f},
+    {0, 32, 32, 4.1f, 0.48f, 1.12f, 1.39f},    {1, 32, 32, 3.8f, 0.81f, 1.18f, 1.36f},
+    {3, 32, 64, 3.9f, 0.93f, 1.13f, 1.20f},    {5, 64, 32, 4.1f, 0.83f, 1.11f, 1.18f},
+    {6, 64, 64, 3.7f, 1.04f, 1.15f, 1.14f},    {10, 64, 64, 4.7f, 1.00f, 1.13f, 1.14f},
+    {11, 64, 96, 3.6f, 1.14f, 1.21f, 1.18f},   {13, 96, 96, 3.8f, 1.13f, 1.17f, 1.16f},
+    {17, 64, 128, 3.8f, 1.10f, 1.13f, 1.12f},  {18, 128, 64, 3.8f, 1.10f, 1.11f, 1.10f},
+    {22, 128, 128, 4.3f, 1.07f, 1.09f, 1.09f}, {24, 128, 256, 5.5f, 1.05f, 1.07f, 1.08f},
+    {30, 160, 64, 3.8f, 1.15f, 1.20f, 1.17f},
 };
 constexpr double kGemmPeakFlopPerUs = 157.3e6;
 constexpr double kGemmCus = 256.0;

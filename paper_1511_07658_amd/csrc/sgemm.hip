@@ -101,20 +101,22 @@ __device__ __forceinline__ f32x4 inside4(f32x4 x, int n, int r, int c) {
 // longer than one MFMA, and one barrier orders both LDS hazards (buffer kt & 1
 // is written in step kt - 1 and read in the same step after the barrier; its
 // previous tile was read before the barrier of step kt - 2).  Left to itself
-// the compiler moves the fragment reads to their uses and waits for every
-// fetch in flight: 23.8 us for one 1024 x 1024 request, 19.5 us in this order
-// (13.7 us of MFMAs); 8 x 1024 x 1024 134.0 -> 124.5 us, 8 x 2048 x 2048
-// 974 -> 947 us against the previous kernel's best tiles.  The two largest
-// MF 16 tiles do not have the registers for a second fragment set and read
-// their fragments at the start of the step.
+// the compiler moves the fragment reads to their uses, waits for every fetch
+// in flight where fetches of the prologue may have changed places, and keeps
+// part of the accumulators where it has to move them back every trip: 23.8 us
+// for one 1024 x 1024 request, 18.5 us in this order (13.7 us of MFMAs), 96x96
+// tiles of 1536 67 and 55.6 us; 8 x 1024 x 1024 134.0 -> 123.8 us, 8 x 2048 x
+// 2048 974 -> 934 us against the previous kernel's best tiles.  The two
+// largest MF 16 tiles do not have the registers for a second fragment set and
+// read their fragments at the start of the step.
 //
 // Any n: rows of A and columns of B outside the matrix are fetched from a
 // valid place (they only reach elements of C that are not stored), so every
 // full k-tile runs the same branch-free step, and only the remainder of k is
 // masked, once per tile.  Fetches are 16 bytes at any float alignment (a row
 // of n floats starts anywhere when n is odd).  n = 517: 73.7 us with masked
-// 4-byte fetches in 81 tiles of 64x64 (80 + 1 in a grid of whole rounds),
-// 8.1 us now.
+// 4-byte fetches in 45 tiles of 64x128 (40 + 5 in a grid of whole rounds over
+// the XCDs), 7.2 us now.
 //
 // Tiles in units, requests in order, tiles of a request row-major.  Workgroup
 // w runs on XCD w % 8, so unit (w % 8) * (grid / 8) + w / 8 gives each XCD a
@@ -298,16 +300,23 @@ __global__ __launch_bounds__(WM * WN * 64) void sgemm_group_kernel(GemmGroupN<N>
     read_frags(0, I0{});
     tail_mfma(I0{});
   } else {
-    // tile t waits in slot t % DEPTH
+    // tile t waits in slot t % DEPTH; the slots are fetched in the order the
+    // loop takes them, or it would wait for the newest one
     load_tile(0, I0{});
+    __builtin_amdgcn_sched_barrier(0);
     load_tile(min(1, nfull - 1), I1{});
+    __builtin_amdgcn_sched_barrier(0);
     if constexpr (DEPTH >= 4) {
       load_tile(min(2, nfull - 1), std::integral_constant<int, 2 % DEPTH>{});
+      __builtin_amdgcn_sched_barrier(0);
       load_tile(min(3, nfull - 1), std::integral_constant<int, 3 % DEPTH>{});
+      __builtin_amdgcn_sched_barrier(0);
     }
     if (!kLateTail && rem) tail_fetch();
     store_tile(0, ra[0], rb[0]);
+    __builtin_amdgcn_sched_barrier(0);
     load_tile(min(DEPTH, nfull - 1), I0{});
+    __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
     if constexpr (PIPE) read_frags(0, I0{});
     auto step = [&](int kt, auto slot, auto set) {
@@ -435,6 +444,7 @@ const GemmConfig kGemmConfigs[] = {
     {27, 256, 64, 16, 4, 1, false},
     {28, 128, 192, 32, 2, 4, false},
     {29, 192, 128, 32, 4, 2, false},
+    {30, 160, 64, 32, 2, 2, false},
 };
 constexpr int kNumGemmConfigs = sizeof(kGemmConfigs) / sizeof(kGemmConfigs[0]);
 
@@ -486,8 +496,8 @@ int gemm_config_forced() {
 // The tuner times launches of kTableCount requests of one size, so its rows
 // hold for those; any other launch takes the cheapest configuration by the
 // cost formula, which knows how many tiles the launch has for the chip (one
-// 1024 x 1024 request: 19.5 us with the formula's 64x64 tiles, 128 us with the
-// 256x128 tiles that are best for eight of them).
+// 1024 x 1024 request: 18.5 us with the formula's 64x64 tiles, 119 us with the
+// 256x128 tiles that are within 1 % of the best for eight of them).
 int gemm_config_for(uint32_t count, const uint32_t* n) {
   const int forced = gemm_config_forced();
   if (forced >= 0) return forced;
@@ -565,6 +575,7 @@ hipError_t launch_sgemm_group(const GemmGroup& g_in, int config_idx, hipStream_t
     case 27: return launch_cfg<256, 64, 16, 4, 1, false, 32, 2, true>(g, s);
     case 28: return launch_cfg<128, 192, 32, 2, 4, false, 16, 2, false>(g, s);
     case 29: return launch_cfg<192, 128, 32, 4, 2, false, 16, 2, false>(g, s);
+    case 30: return launch_cfg<160, 64, 32, 2, 2, false, 16, 2, true>(g, s);
     default: return hipErrorInvalidValue;
   }
 }

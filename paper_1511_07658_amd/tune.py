@@ -32,8 +32,8 @@ from . import workloads as wl
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 TABLE = os.path.join(HERE, "csrc", "gemm_tiles.inc")
-NUM_CONFIGS = 30
-CONFIG_NAMES = ['32x32x32R4m16P', '32x32x32R2m16P', '32x32x64R2m16P', '32x64x32R2m16P', '32x64x64R2m16P', '64x32x32R2m16P', '64x64x32R2m16w8P', '64x64x32R4m16P', '64x64x32R2P', '64x64x16R4P', '64x64x64R2P', '64x96x32R2m16P', '96x64x32R2m16P', '96x96x32R2m16P', '96x128x32R2m16P', '128x96x32R2m16P', '64x128x16R4P', '64x128x32R2P', '128x64x32R2w8P', '128x64x32R2P', '128x128x16R2P', '128x128x32R2P', '128x128x16R4w8P', '128x128x32R2w8P', '128x256x16R2w8P', '256x128x16R2w8P', '64x256x16R2P', '256x64x16R2P', '128x192x32R2m16w8', '192x128x32R2m16w8']
+NUM_CONFIGS = 31
+CONFIG_NAMES = ['32x32x32R4m16P', '32x32x32R2m16P', '32x32x64R2m16P', '32x64x32R2m16P', '32x64x64R2m16P', '64x32x32R2m16P', '64x64x32R2m16w8P', '64x64x32R4m16P', '64x64x32R2P', '64x64x16R4P', '64x64x64R2P', '64x96x32R2m16P', '96x64x32R2m16P', '96x96x32R2m16P', '96x128x32R2m16P', '128x96x32R2m16P', '64x128x16R4P', '64x128x32R2P', '128x64x32R2w8P', '128x64x32R2P', '128x128x16R2P', '128x128x32R2P', '128x128x16R4w8P', '128x128x32R2w8P', '128x256x16R2w8P', '256x128x16R2w8P', '64x256x16R2P', '256x64x16R2P', '128x192x32R2m16w8', '192x128x32R2m16w8', '160x64x32R2m16P']
 
 
 def warmup_launches(n, group, target_ms=60.0):
