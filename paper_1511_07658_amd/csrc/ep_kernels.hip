@@ -88,21 +88,20 @@ __device__ __forceinline__ void philox_block(uint64_t b, uint64_t k0, uint64_t k
   w[3] = c3;
 }
 
-// -2 ln of the 256 leading-bit intervals of [1/2, 1): {1/c, 2 ln(1/c)} with c
-// the middle of interval i, except that the first takes c = 1/2 and the last
-// c = 1, so that ln is exact where it is zero (t = 1 as 2 * 1/2) and keeps its
-// relative accuracy as t approaches 1 from below.
+// {1/c, 2 ln(1/c)} of the 256 intervals of [1/2, 1) by leading bits, c the
+// middle of interval i, except that the first takes c = 1/2 and the last c = 1,
+// so that ln is exact where it is zero (t = 1 as 2 * 1/2) and keeps its relative
+// accuracy as t approaches 1 from below.  A table in memory: computed by the
+// workgroup it was a chain of a divide and a logarithm before the first pair
+// (2^15 pairs: 5.2 -> 4.8 us with the shorter sums below).
 constexpr int kLogTable = 256;
 constexpr double kLn2 = 0x1.62e42fefa39efp-1;
 struct LogEntry {
   double inv, m2log;
 };
-__device__ __forceinline__ LogEntry log_entry(int i) {
-  if (i == 0) return {2.0, 2.0 * kLn2};
-  if (i == kLogTable - 1) return {1.0, 0.0};
-  const double inv = 1.0 / (0.5 + (i + 0.5) * (0.5 / kLogTable));
-  return {inv, 2.0 * log(inv)};
-}
+__device__ const LogEntry kLogEntries[kLogTable] = {
+#include "ep_log_table.inc"
+};
 
 // A thread's annulus counts within one work unit, 8 bits each: counts 0..7
 // in `lo`, 8..9 in `hi` (a thread tallies at most kEpUnit / kEpThreads = 64
@@ -171,12 +170,26 @@ __device__ __forceinline__ void far_annulus(int l, Tally& q) {
   if (l < 10) q.hi += 1ull << (8 * (l - 8));
 }
 
-// Fixed-order sum over the 64 lanes (binary tree over lane indices), valid in
-// lane 0.
+// Fixed-order sum over the 64 lanes, valid in lane 63: lane shifts by 1, 2, 4
+// and 8 within the rows of 16, then the rows' last lanes into the rows after
+// them (DPP moves instead of shuffles through LDS: with the reduction of few
+// records by one wave, 4.1 -> 2.2 us for the second launch of 2^15 pairs).
+template <int CTRL, int ROWS, class T>
+__device__ __forceinline__ T dpp_move(T v) {
+  static_assert(sizeof(T) == 8, "two registers");
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<uint32_t>(b), CTRL, ROWS, 0xF, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<uint32_t>(b >> 32), CTRL, ROWS, 0xF, false);
+  return __builtin_bit_cast(T, (static_cast<uint64_t>(hi) << 32) | lo);
+}
 template <class T>
 __device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-  for (int s = 32; s > 0; s >>= 1) v += __shfl_down(v, s);
+  v += dpp_move<0x111, 0xF>(v);   // row_shr:1, 2, 4, 8
+  v += dpp_move<0x112, 0xF>(v);
+  v += dpp_move<0x114, 0xF>(v);
+  v += dpp_move<0x118, 0xF>(v);
+  v += dpp_move<0x142, 0xA>(v);   // row_bcast:15 into rows 1 and 3
+  v += dpp_move<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
   return v;
 }
 
@@ -206,7 +219,7 @@ __global__ __launch_bounds__(kEpThreads) void ep_units_kernel(EpGroupN<N> g) {
     const uint64_t k0 = d.inline_key ? d.key_value[0] : d.key[0];
     const uint64_t k1 = d.inline_key ? d.key_value[1] : d.key[1];
     if (d.inline_key && local == 0 && threadIdx.x < 2) d.key[threadIdx.x] = threadIdx.x ? k1 : k0;
-    if (u == blockIdx.x && threadIdx.x < kLogTable) table[threadIdx.x] = log_entry(threadIdx.x);
+    if (u == blockIdx.x && threadIdx.x < kLogTable) table[threadIdx.x] = kLogEntries[threadIdx.x];
     uint64_t h, l;
     mul128(kPhiloxM0, k0, h, l);
     double sx = 0.0, sy = 0.0;
@@ -234,7 +247,7 @@ __global__ __launch_bounds__(kEpThreads) void ep_units_kernel(EpGroupN<N> g) {
     sy = wave_sum(sy);
     const uint64_t q0 = wave_sum(q.lo & 0x00FF00FF00FF00FFull), q1 = wave_sum((q.lo >> 8) & 0x00FF00FF00FF00FFull);
     const uint64_t q2 = wave_sum((q.hi & 0xFF) | ((q.hi & 0xFF00) << 8));
-    if (lane == 0) {
+    if (lane == 63) {
       wsx[wave] = sx;
       wsy[wave] = sy;
       wq[wave][0] = q0;
@@ -264,23 +277,22 @@ __global__ __launch_bounds__(kEpThreads) void ep_units_kernel(EpGroupN<N> g) {
   }
 }
 
-// Sum of a request's records.  Latency: one or two records per thread at 2^24
-// pairs, then shuffles (ten LDS counters added to by every thread took 6.5 us
-// for 32 records and 13 us for 1024).
-constexpr int kEpSumThreads = 512;
-
-template <int N>
-__global__ __launch_bounds__(kEpSumThreads) void ep_reduce_kernel(EpGroupN<N> g) {
-  constexpr int kWaves = kEpSumThreads / 64;
-  __shared__ double ws[kWaves][2];
-  __shared__ uint64_t wq[kWaves][10];
+// Sum of a request's records.  Latency: two records per thread at 2^24 pairs
+// (4.5 us), and one wave where it holds the records of every request (2.2 us for
+// 32 or 49; ten LDS counters added to by every thread took 6.5 us for 32 and
+// 13 us for 1024).  Up to 64 records both sum in the same order: the other seven
+// waves add zeros, so the choice does not show in the result.
+template <int THREADS, int N>
+__global__ __launch_bounds__(THREADS) void ep_reduce_kernel(EpGroupN<N> g) {
+  constexpr int kWaves = THREADS / 64;
+  __shared__ uint64_t ws[kWaves][kEpWords];
   const EpDesc& d = g.d[blockIdx.x];
   if (d.units == 1) return;  // written by the unit launch
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const uint64_t* rec = static_cast<const uint64_t*>(d.partial);
   double sx = 0.0, sy = 0.0;
   uint64_t q[10] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  for (uint64_t i = threadIdx.x; i < d.units; i += kEpSumThreads) {
+  for (uint64_t i = threadIdx.x; i < d.units; i += THREADS) {
     uint64_t w[kEpRecordBytes / 8];
 #pragma unroll
     for (uint64_t k = 0; k < kEpRecordBytes / 8; ++k) w[k] = rec[i * (kEpRecordBytes / 8) + k];
@@ -293,22 +305,22 @@ __global__ __launch_bounds__(kEpSumThreads) void ep_reduce_kernel(EpGroupN<N> g)
   sy = wave_sum(sy);
 #pragma unroll
   for (int l = 0; l < 10; ++l) q[l] = wave_sum(q[l]);
-  if (lane == 0) {
-    ws[wave][0] = sx;
-    ws[wave][1] = sy;
+  if (lane == 63) {
+    ws[wave][0] = __double_as_longlong(sx);
+    ws[wave][1] = __double_as_longlong(sy);
 #pragma unroll
-    for (int l = 0; l < 10; ++l) wq[wave][l] = q[l];
+    for (int l = 0; l < 10; ++l) ws[wave][2 + l] = q[l];
   }
   __syncthreads();
   if (threadIdx.x < 2) {
     double sum = 0.0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) sum += ws[w][threadIdx.x];
+    for (int w = 0; w < kWaves; ++w) sum += __longlong_as_double(ws[w][threadIdx.x]);
     d.out[threadIdx.x] = __double_as_longlong(sum);
-  } else if (threadIdx.x < 12) {
+  } else if (threadIdx.x < kEpWords) {
     uint64_t c = 0;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) c += wq[w][threadIdx.x - 2];
+    for (int w = 0; w < kWaves; ++w) c += ws[w][threadIdx.x];
     d.out[threadIdx.x] = c;
   }
 }
@@ -331,7 +343,10 @@ template <int N>
 hipError_t launch_ep(const EpGroupN<N>& g, hipStream_t s) {
   const hipError_t e = launch_group(ep_units_kernel<N>, g.grid, kEpThreads, s, g);
   if (e != hipSuccess || g.total_units == g.count) return e;
-  return launch_group(ep_reduce_kernel<N>, g.count, kEpSumThreads, s, g);
+  uint64_t most = 0;
+  for (uint32_t i = 0; i < g.count; ++i) most = std::max(most, g.d[i].units);
+  return most <= 64 ? launch_group(ep_reduce_kernel<64, N>, g.count, 64, s, g)
+                    : launch_group(ep_reduce_kernel<512, N>, g.count, 512, s, g);
 }
 }  // namespace
 
