@@ -124,18 +124,20 @@ void CopyEngine::submit(void* dst, const void* src, size_t bytes, std::atomic<in
     copy(static_cast<char*>(dst), static_cast<const char*>(src), bytes);
     return;
   }
-  // Eight chunks, so that the workers share a copy that something waits for
-  // (the first input of a batch, whose transfer starts the link, and its last
-  // result): 8 ranks of SGEMM 1024 with copies 1.80 -> 1.67 ms against chunks
-  // of 4 MiB, 16 ranks of 4M options 15.9 -> 15.5.  Chunks of 4 MiB stay the
-  // largest for the longest copies, where many small ones cost the queue more
-  // than they give (32 uneven ranks, 1.1 GB: 15.3-15.5 ms either way, 15.4-15.7
-  // with 1 MiB throughout).
-  const size_t chunk = std::min(kMaxChunk, std::max(kMinChunk, (bytes / 8 + 4095) & ~size_t(4095)));
-  const size_t n = (bytes + chunk - 1) / chunk;
-  pending->fetch_add(static_cast<int>(n), std::memory_order_acq_rel);
+  // Chunks of 4 MiB, but eight chunks (512 KiB and more) for a copy that finds
+  // nothing queued, so that the workers share what something waits for (the
+  // first input of a batch, whose transfer starts the link, and its last
+  // result): 8 ranks of SGEMM 1024 with copies 1.85 -> 1.72 ms.  Behind other
+  // copies there is nothing to share, and small chunks cost throughput: 64
+  // ranks at 1000 requests/s of 0.25-64 MiB saw p50 2.5 -> 28-66 ms and p99
+  // 60 -> 800 ms when every copy was cut into eight.
+  const size_t eighth = std::min(kMaxChunk, std::max(kMinChunk, (bytes / 8 + 4095) & ~size_t(4095)));
+  size_t n;
   {
     std::lock_guard<std::mutex> lk(mu_);
+    const size_t chunk = queue_.empty() && urgent_.empty() ? eighth : kMaxChunk;
+    n = (bytes + chunk - 1) / chunk;
+    pending->fetch_add(static_cast<int>(n), std::memory_order_acq_rel);
     std::deque<Chunk>& q = urgent ? urgent_ : queue_;
     for (size_t i = 0; i < n; ++i) {
       const size_t off = i * chunk;
