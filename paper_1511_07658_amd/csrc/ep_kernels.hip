@@ -114,11 +114,14 @@ struct Tally {
 };
 
 // 2^63 (2u - 1) with u = (w >> 11) 2^-53, exactly: the word's upper 53 bits
-// as a signed number.
+// less 2^63.  The halves stand as the low mantissa words of 2^84 and 2^52; both
+// sums are exact (2^27 pairs: 448 -> 436 us against two conversions and a
+// multiply-add).
 __device__ __forceinline__ double centred(uint64_t w) {
-  const int32_t hi = static_cast<int32_t>(static_cast<uint32_t>(w >> 32) ^ 0x80000000u);
-  const uint32_t lo = static_cast<uint32_t>(w) & 0xFFFFF800u;
-  return __builtin_fma(static_cast<double>(hi), 0x1p32, static_cast<double>(lo));
+#pragma clang fp contract(off)
+  const double hi = __longlong_as_double(0x4530000000000000ull | (w >> 32));             // 2^84 + 2^32 (w >> 32)
+  const double lo = __longlong_as_double(0x4330000000000000ull | (w & 0xFFFFF800ull));   // 2^52 + the lower bits
+  return (hi - (0x1p84 + 0x1p63 + 0x1p52)) + lo;
 }
 
 // One pair from two generator words: accept it when 0 < t <= 1, add its
@@ -200,10 +203,13 @@ struct EpRecord {
 };
 static_assert(sizeof(EpRecord) == kEpRecordBytes, "record layout");
 
-// Bound by VALU issue: a SIMD takes 4 cycles per wave64 instruction, binary64
-// and 32-bit multiplies included.  8 waves per workgroup on small units fill
-// the SIMDs for requests of any size (a unit of 2^15 pairs on 256 threads left
-// a request of 2^15 pairs to one CU: 88 us).
+// Bound by VALU issue: with two waves or more on a SIMD a wave64 instruction
+// takes 4 cycles in binary64, in 64-bit integers and for 32-bit multiplies, a
+// plain 32-bit one 2 and a binary64 root 16 (measured with loops of one kind).
+// The 271 of two pairs come to about 880 cycles that way; a request of 2^27
+// pairs runs at 307 Gpairs/s, 1024 cycles at 2.4 GHz.  8 waves per workgroup on
+// small units fill the SIMDs for requests of any size (a unit of 2^15 pairs on
+// 256 threads left a request of 2^15 pairs to one CU: 88 us).
 template <int N>
 __global__ __launch_bounds__(kEpThreads) void ep_units_kernel(EpGroupN<N> g) {
   __shared__ LogEntry table[kLogTable];
