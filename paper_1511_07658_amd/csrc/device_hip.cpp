@@ -71,23 +71,25 @@ struct Batch {
 // uneven launch: 487 us, against 489-490 us with 64x128 and 128x64 tiles of
 // four waves, 494-496 with 64x64 and 505 and more with 128x128).  Everything
 // else is chosen by gemm_config_for.  Tuning override for mixed sizes:
-// GVM_SGEMM_MIX_CONFIG=<index>.
+// GVM_SGEMM_MIX_CONFIG=<index>.  In a masked partition the
+// tiles are counted over its `cus` (0: no mask): 2048^2 requests on 192 CUs
+// ran at 70 TFLOP/s with the tiles that suit 256 and run at 91.
 constexpr int kMixConfig = 18;
 
-int gemm_group_config(const GemmGroup& g) {
+int gemm_group_config(const GemmGroup& g, int cus) {
   const GemmConfig& mix = gemm_config(kMixConfig);
   uint64_t tiles = 0;
   for (uint32_t i = 0; i < g.count; ++i) {
     const uint64_t n = g.d[i].n;
     tiles += ((n + mix.bm - 1) / mix.bm) * ((n + mix.bn - 1) / mix.bn);
   }
-  if (g.d[0].n == g.d[g.count - 1].n) return gemm_config_for(g);
+  if (g.d[0].n == g.d[g.count - 1].n) return gemm_config_for(g, cus);
   static const int env = [] {
     const char* e = getenv("GVM_SGEMM_MIX_CONFIG");
     return e ? atoi(e) : -1;
   }();
   if (env >= 0 && env < gemm_config_count()) return env;
-  return tiles >= 2 * kPartitionCus ? kMixConfig : gemm_config_for(g);
+  return tiles >= 2 * static_cast<uint64_t>(cus ? cus : kPartitionCus) ? kMixConfig : gemm_config_for(g, cus);
 }
 
 // Order of a grouped batch's launches: 0 = dealt over both compute streams,
@@ -699,6 +701,21 @@ class HipDevice final : public Device {
     return GVM_OK;
   }
 
+  // CUs that carry an SGEMM launch of the masked partition a job runs in, 0
+  // outside one.  Workgroups are dealt evenly to the shader engines (bits 3-4
+  // of a CU's index) that have a CU, so the one with the fewest sets the rate:
+  // 224 CUs with one engine halved ran 2048^2 at 70 TFLOP/s, as 128 would.
+  int part_cus(const Job* j) const {
+    if (j->part < 0 || part_streams_.size() != 2 || !part_masked_) return 0;
+    int engines = 0, fewest = kPartitionCus;
+    for (uint32_t b = 0; b < 4; ++b) {
+      int n = 0;
+      for (uint32_t w : part_mask_[j->part]) n += __builtin_popcount(w & (0xFFu << (8 * b)));
+      if (n) ++engines, fewest = std::min(fewest, n);
+    }
+    return engines * fewest;
+  }
+
   // The plan's view of a job (one with inline_io has no copies, and completes
   // with its launch).
   static PlanJob plan_job(const Job* j) {
@@ -786,7 +803,7 @@ class HipDevice final : public Device {
         gg.d[i].C = reinterpret_cast<float*>(v[i]->slot + slot_out_offset(v[i]->lay));
         gg.d[i].n = static_cast<uint32_t>(n);
       }
-      const int cfgi = gemm_group_config(gg);
+      const int cfgi = gemm_group_config(gg, part_cus(v[0]));
       finalize_gemm_group(gg, cfgi);
       if ((e = mark()) == hipSuccess) e = launch_sgemm_group(gg, cfgi, s);
     } else if (k == GVM_K_EP) {

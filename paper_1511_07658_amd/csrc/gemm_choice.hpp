@@ -9,11 +9,12 @@ namespace gvm {
 
 // Time of a launch under one tile configuration, in us:
 //
-//   t0 + W / peak * (k / x) * e_k,   x = tiles / 256,  k = ceil(x)
+//   t0 + W / peak * (k / x) * e_k,   x = tiles / CUs,  k = ceil(x)
 //
 // with W the FLOP of the whole tiles (ragged edges padded to the tile, as the
-// kernel computes them), 157.3 TFLOP/s the chip's FP32 matrix rate, x the
-// tiles per CU and k / x what the fullest CU has more than the mean.  t0 is
+// kernel computes them), peak the FP32 matrix rate of the CUs the launch may
+// use (157.3 TFLOP/s for all 256; a masked partition has fewer), x the tiles
+// per CU and k / x what the fullest CU has more than the mean.  t0 is
 // the part no tile size takes away (launch, first fetch, store of C); e1, e2
 // and e3 are the inverse of the rate a CU reaches with one, two and more tiles
 // (one tile alone has nothing to hide its barriers and fetches behind).  t0
@@ -37,8 +38,8 @@ constexpr GemmCost kGemmCosts[] = {
     {22, 128, 128, 4.3f, 1.07f, 1.09f, 1.09f}, {24, 128, 256, 5.5f, 1.05f, 1.07f, 1.08f},
     {30, 160, 64, 3.8f, 1.15f, 1.20f, 1.17f},
 };
-constexpr double kGemmPeakFlopPerUs = 157.3e6;
-constexpr double kGemmCus = 256.0;
+constexpr int kGemmCus = 256;
+constexpr double kGemmPeakFlopPerUs = 157.3e6 / kGemmCus;   // of one CU
 
 inline uint64_t gemm_tiles(const GemmCost& c, uint64_t n) {
   return ((n + c.bm - 1) / c.bm) * ((n + c.bn - 1) / c.bn);
@@ -48,7 +49,7 @@ inline uint64_t gemm_tiles(const GemmCost& c, uint64_t n) {
 // long one; its share of that (half, as measured on the 32-rank uneven mix)
 // is added to the mean time, or the mean to the longest tile where that is
 // the longer of the two.
-inline double gemm_launch_us(const GemmCost& c, uint32_t count, const uint32_t* n) {
+inline double gemm_launch_us(const GemmCost& c, uint32_t count, const uint32_t* n, int cus) {
   double flop = 0.0, tiles = 0.0;
   uint32_t nmax = 0, nmin = ~0u;
   for (uint32_t i = 0; i < count; ++i) {
@@ -58,21 +59,23 @@ inline double gemm_launch_us(const GemmCost& c, uint32_t count, const uint32_t* 
     nmax = std::max(nmax, n[i]);
     nmin = std::min(nmin, n[i]);
   }
-  const double x = tiles / kGemmCus;
+  const double x = tiles / cus;
   const double k = static_cast<double>(static_cast<uint64_t>(x) + (x > static_cast<uint64_t>(x) ? 1 : 0));
   const double e = k <= 1 ? c.e1 : k <= 2 ? c.e2 : c.e3;
-  const double mean = flop / kGemmPeakFlopPerUs * e;
+  const double peak = kGemmPeakFlopPerUs * cus;
+  const double mean = flop / peak * e;
   if (nmin == nmax) return c.t0 + mean * k / x;
-  const double longest = 2.0 * c.bm * c.bn * nmax * kGemmCus / kGemmPeakFlopPerUs * e;
+  const double longest = 2.0 * c.bm * c.bn * nmax * cus / peak * e;
   return c.t0 + std::max(mean, longest) + 0.5 * std::min(mean, longest);
 }
 
-// The cheapest configuration for one launch of requests of sizes n[0..count).
-inline int gemm_cheapest(uint32_t count, const uint32_t* n) {
+// The cheapest configuration for one launch of requests of sizes n[0..count)
+// on `cus` CUs.
+inline int gemm_cheapest(uint32_t count, const uint32_t* n, int cus = kGemmCus) {
   int best = kGemmCosts[0].config;
   double t_best = 0.0;
   for (const GemmCost& c : kGemmCosts) {
-    const double t = gemm_launch_us(c, count, n);
+    const double t = gemm_launch_us(c, count, n, cus);
     if (&c == &kGemmCosts[0] || t < t_best) {
       t_best = t;
       best = c.config;

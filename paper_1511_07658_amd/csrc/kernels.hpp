@@ -119,9 +119,9 @@ struct GemmConfig {
 int gemm_config_count();
 const GemmConfig& gemm_config(int idx);
 // Tile configuration of one launch of the sizes n[0 .. count), or of a group
-// whose sizes are filled in.
-int gemm_config_for(uint32_t count, const uint32_t* n);
-int gemm_config_for(const GemmGroup& g);
+// whose sizes are filled in, on `cus` of the chip's CUs (0: all).
+int gemm_config_for(uint32_t count, const uint32_t* n, int cus = 0);
+int gemm_config_for(const GemmGroup& g, int cus = 0);
 // The configuration forced for every launch (by gemm_config_force or the
 // environment), or -1.
 int gemm_config_forced();

@@ -498,21 +498,21 @@ int gemm_config_forced() {
 // cost formula, which knows how many tiles the launch has for the chip (one
 // 1024 x 1024 request: 18.5 us with the formula's 64x64 tiles, 119 us with the
 // 256x128 tiles that are within 1 % of the best for eight of them).
-int gemm_config_for(uint32_t count, const uint32_t* n) {
+int gemm_config_for(uint32_t count, const uint32_t* n, int cus) {
   const int forced = gemm_config_forced();
   if (forced >= 0) return forced;
   constexpr uint32_t kTableCount = 8, kTableStep = 64;
-  bool table = count == kTableCount && n[0] % kTableStep == 0;
+  bool table = count == kTableCount && n[0] % kTableStep == 0 && !cus;
   for (uint32_t i = 1; i < count; ++i) table &= n[i] == n[0];
   if (table)
     for (const auto& row : kTileTable)
       if (n[0] <= row[0] && row[0] < kTileTableEnd) return static_cast<int>(row[1]);
-  return gemm_cheapest(count, n);
+  return gemm_cheapest(count, n, cus ? cus : kGemmCus);
 }
-int gemm_config_for(const GemmGroup& g) {
+int gemm_config_for(const GemmGroup& g, int cus) {
   uint32_t n[kMaxGroup];
   for (uint32_t i = 0; i < g.count; ++i) n[i] = g.d[i].n;
-  return gemm_config_for(g.count, n);
+  return gemm_config_for(g.count, n, cus);
 }
 void finalize_gemm_group(GemmGroup& g, int config_idx) {
   const GemmConfig& c = kGemmConfigs[config_idx];
