@@ -69,29 +69,31 @@ MAX_GPU_PROCESSES = 16
 # 64-bit integer products, which dominate the kernel, are not in the count.
 EP_FP64_OPS_PER_PAIR = 9.0 + math.pi / 4.0 * 9.0
 # VALU issue utilisation of the compiled kernel (a diagnostic of the code,
-# not a roofline): the unit loop of csrc/ep_kernels.hip issues 602 wave64
-# VALU instructions per Philox block (2 pairs per lane, both accepted), one
-# per 4 cycles per SIMD: 4 * 602 / 128 SIMD cycles per pair.
-EP_SIMD_CYCLES_PER_PAIR = 4.0 * 602 / 128
+# not a roofline): per Philox block (2 pairs per lane, both accepted) the unit
+# loop of csrc/ep_kernels.hip issues 271 wave64 VALU instructions: 171 of 4
+# cycles (binary64, 64-bit integer, 32-bit multiplies and compares), 98 plain
+# 32-bit ones of 2 and 2 binary64 roots of 16, the costs measured with loops of
+# one kind at two and more waves per SIMD.
+EP_SIMD_CYCLES_PER_PAIR = (171 * 4.0 + 98 * 2.0 + 2 * 16.0) / 128
 EP_ISSUE_GPAIRS = 256 * 4 * 2.4e9 / EP_SIMD_CYCLES_PER_PAIR / 1e9
 
 # HBM bytes per launch of the dominant kernel from rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE (KiB per dispatch), each scaled by what the counter reads for a
 # plain 1 GiB copy (fetch x2.000, write x1.000); valid only for the kernel
 # sources they were taken on (sha256 over `sources` in csrc/, in order;
-# profiles/mixed32_uneven.md, profiles/sgemm_grouped_8x1024.md,
-# profiles/blackscholes_grouped_16x4M.md, profiles/vecadd_grouped_16x16M.md).
-SGEMM_SOURCES = ("sgemm.hip", "group_device.hpp", "kernels.hpp", "gemm_tiles.inc", "gemm_balance.hpp")
+# profiles/kernel_traces_and_counters.md).
+SGEMM_SOURCES = ("sgemm.hip", "group_device.hpp", "kernels.hpp", "gemm_tiles.inc", "gemm_choice.hpp",
+                 "gemm_balance.hpp")
 STREAM_SOURCES = ("stream_kernels.hip", "group_device.hpp", "kernels.hpp")
 MEASURED_TRAFFIC = {
-    "mixed32": {"sources": SGEMM_SOURCES, "kernels_sha256": "3d2c051e13bf44668076478faae892d99794840189aad7e4a9d42bb5e104c64e",
-                "fetch_kib": 459439.1, "fetch_factor": 2.000, "write_kib": 85152.0, "write_factor": 1.000},
-    "sgemm8": {"sources": SGEMM_SOURCES, "kernels_sha256": "3d2c051e13bf44668076478faae892d99794840189aad7e4a9d42bb5e104c64e",
-               "fetch_kib": 32838.3, "fetch_factor": 2.000, "write_kib": 32768.0, "write_factor": 1.000},
-    "bs16": {"sources": STREAM_SOURCES, "kernels_sha256": "8fe15074feb50f84a1329d139469e3f76e1f9b34fe8eeb59000d99b7b62abbab",
-             "fetch_kib": 393326.6, "fetch_factor": 2.000, "write_kib": 524300.7, "write_factor": 1.000},
-    "vecadd16": {"sources": STREAM_SOURCES, "kernels_sha256": "8fe15074feb50f84a1329d139469e3f76e1f9b34fe8eeb59000d99b7b62abbab",
-                 "fetch_kib": 1048597.1, "fetch_factor": 2.000, "write_kib": 1048576.0, "write_factor": 1.000},
+    "mixed32": {"sources": SGEMM_SOURCES, "kernels_sha256": "cad9c1fd38d1062206dfb19bc0ce900bf65e1d64a7e55ef74dc590413e4104ba",
+                "fetch_kib": 453902.0, "fetch_factor": 2.000, "write_kib": 85152.0, "write_factor": 1.000},
+    "sgemm8": {"sources": SGEMM_SOURCES, "kernels_sha256": "cad9c1fd38d1062206dfb19bc0ce900bf65e1d64a7e55ef74dc590413e4104ba",
+               "fetch_kib": 32857.4, "fetch_factor": 2.000, "write_kib": 32768.0, "write_factor": 1.000},
+    "bs16": {"sources": STREAM_SOURCES, "kernels_sha256": "073ce6a597552763cc336c5dba9c28759575aced10567c93a84c9bd4e901bff1",
+             "fetch_kib": 393307.5, "fetch_factor": 2.000, "write_kib": 524288.9, "write_factor": 1.000},
+    "vecadd16": {"sources": STREAM_SOURCES, "kernels_sha256": "073ce6a597552763cc336c5dba9c28759575aced10567c93a84c9bd4e901bff1",
+                 "fetch_kib": 1048598.0, "fetch_factor": 2.000, "write_kib": 1048576.0, "write_factor": 1.000},
 }
 
 

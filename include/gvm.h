@@ -301,13 +301,13 @@ int gvm_plain_run(int kernel_id, const void* in, void* out, uint64_t n,
  * that forbid hipMalloc.  It enqueues the same kernel code objects on
  * caller-owned device buffers and returns without waiting:
  *   d_in    device memory of the current device holding the packed input of
- *           the request (layouts above); 16-byte alignment gives the
- *           vectorised SGEMM loads;
+ *           the request (layouts above), at any alignment of its elements;
  *   d_out   device memory receiving the packed output;
  *   stream  a hipStream_t of the current device (NULL: the null stream).
  * The caller owns both buffers and synchronises the stream before reading
  * d_out.  It calls no hipMalloc, hipFree or allocating routine.  The EP-like
- * kernel's per-unit partial records (96 bytes per 2^15 pairs) go to a static
+ * kernel's partial records (at most 96 bytes per 2^15 pairs, or 3584 bytes
+ * where that is more) go to a static
  * device array of GVM_NOALLOC_SCRATCH_BYTES per GPU, held until the process
  * ends; an EP request needing more (n > 357,892,096 pairs) returns
  * GVM_ENOMEM before anything is enqueued.  Every call on one GPU shares that

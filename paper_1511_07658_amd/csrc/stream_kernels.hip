@@ -26,11 +26,20 @@ namespace {
 // register-limited occupancy and balances the tail.  Results are stored
 // non-temporal at any size: nothing here reads them back, and the 256 MB
 // memory-side cache keeps the inputs instead (vector add of 2^22 read again:
-// 6.9 us, 8.4 with cached stores).  Inputs are loaded cached up to kCachedInput
-// bytes, with 2 float4 per thread (8M elements 15.2 us, 16.7 non-temporal);
-// beyond it non-temporal with 4 (16M: 31.8 us, 35.0 cached; 14.5M 27.6 and
-// 30.0; at 12.6M, 100 MB of input, the two meet).
+// 6.9 us, 8.4 with cached stores).  Inputs are loaded
+//  * cached up to kCachedInput bytes of them, with 2 float4 per thread (8M
+//    elements 15.0 us, 16.7 non-temporal);
+//  * beyond it with 4 float4 per thread, the last operand (b, T) cached where
+//    it alone stays within kCachedInput and the others non-temporal: that
+//    operand is then read from the memory-side cache the next time (16M
+//    elements 29.3 us, 31.7 all non-temporal, 34.6 all cached; 14.5M 26.0, 27.5
+//    and 29.8; 16M options 52.9 and 57.8), and a wave that starts inside a line
+//    finds it there (b of odd length on its first pass: 36.5 us, 40.3 all
+//    non-temporal);
+//  * all non-temporal beyond that (three buffers of 33.5M in turn: 61.8 us, 63.0
+//    with b cached; 134M 251 and 257).
 constexpr uint64_t kCachedInput = 96ull << 20;
+enum Loads { kAllCached, kLastCached, kNoneCached };
 
 // ---------------------------------------------------------------- vectors
 
@@ -57,7 +66,7 @@ __device__ __forceinline__ f32x4 op4(Op op, f32x4 a, f32x4 b) {
 // Bound by memory.  The operands of a request of odd length start anywhere
 // (b is a + n), so every access is 16 bytes at float alignment: 14.5M elements
 // 27.6 us (6.3 TB/s, as 2^24 has), 34.8 element by element.
-template <class Op, int V4, bool NT, int N>
+template <class Op, int V4, Loads LOADS, int N>
 __global__ __launch_bounds__(kThreads) void vec_group_kernel(VecGroupN<N> g) {
   constexpr uint64_t kUnit = V4 * 4 * kThreads;
   Op op;
@@ -72,8 +81,8 @@ __global__ __launch_bounds__(kThreads) void vec_group_kernel(VecGroupN<N> g) {
       f32x4 va[V4], vb[V4];
 #pragma unroll
       for (int j = 0; j < V4; ++j) {
-        va[j] = stream_load<f32x4u, NT>(a4 + threadIdx.x + j * kThreads);
-        vb[j] = stream_load<f32x4u, NT>(b4 + threadIdx.x + j * kThreads);
+        va[j] = stream_load<f32x4u, LOADS != kAllCached>(a4 + threadIdx.x + j * kThreads);
+        vb[j] = stream_load<f32x4u, LOADS == kNoneCached>(b4 + threadIdx.x + j * kThreads);
       }
 #pragma unroll
       for (int j = 0; j < V4; ++j) stream_store<f32x4u>(op4(op, va[j], vb[j]), c4 + threadIdx.x + j * kThreads);
@@ -166,7 +175,7 @@ __device__ __forceinline__ bool bs_extreme(float S, float K) {
   return !SAFE && !(plain_range(K) && fabsf(S) <= 0x1p100f);
 }
 
-template <bool SAFE, int V4, bool NT>
+template <bool SAFE, int V4, Loads LOADS>
 __device__ __forceinline__ void bs_quads(const BsDesc& d, uint64_t e, const BsParams& c) {
   const f32x4u* S4 = reinterpret_cast<const f32x4u*>(d.S + e);
   const f32x4u* K4 = reinterpret_cast<const f32x4u*>(d.K + e);
@@ -174,9 +183,9 @@ __device__ __forceinline__ void bs_quads(const BsDesc& d, uint64_t e, const BsPa
   f32x4 S[V4], K[V4], T[V4];
 #pragma unroll
   for (int j = 0; j < V4; ++j) {
-    S[j] = stream_load<f32x4u, NT>(S4 + j * kThreads);
-    K[j] = stream_load<f32x4u, NT>(K4 + j * kThreads);
-    T[j] = stream_load<f32x4u, NT>(T4 + j * kThreads);
+    S[j] = stream_load<f32x4u, LOADS != kAllCached>(S4 + j * kThreads);
+    K[j] = stream_load<f32x4u, LOADS != kAllCached>(K4 + j * kThreads);
+    T[j] = stream_load<f32x4u, LOADS == kNoneCached>(T4 + j * kThreads);
   }
 #pragma unroll
   for (int j = 0; j < V4; ++j) {
@@ -209,7 +218,7 @@ __device__ __forceinline__ void bs_quads(const BsDesc& d, uint64_t e, const BsPa
 // the 6.17 TB/s of its access mix.  17.6 us with 102 instructions per option
 // (75 now); 300001 options 8.3 us element by element in 74 units of 4096, now
 // 3.8 in units of 2048.
-template <int V4, bool NT, bool SAFE, int N>
+template <int V4, Loads LOADS, bool SAFE, int N>
 __global__ __launch_bounds__(kThreads) void bs_group_kernel(BsGroupN<N> g) {
   constexpr uint64_t kUnit = V4 * 4 * kThreads;
   const BsParams c{g.rate, g.volatility, 1.0f / g.volatility, 0.5f * g.volatility * g.volatility};
@@ -218,11 +227,11 @@ __global__ __launch_bounds__(kThreads) void bs_group_kernel(BsGroupN<N> g) {
     const uint64_t e0 = (u - d.unit_begin) * kUnit;
     const uint64_t left = d.n - e0;
     if (left >= kUnit) {
-      bs_quads<SAFE, V4, NT>(d, e0 + 4 * threadIdx.x, c);
+      bs_quads<SAFE, V4, LOADS>(d, e0 + 4 * threadIdx.x, c);
     } else {
       for (uint64_t e = 4 * threadIdx.x; e < left; e += 4 * kThreads) {
         if (e + 4 <= left) {
-          bs_quads<SAFE, 1, NT>(d, e0 + e, c);
+          bs_quads<SAFE, 1, LOADS>(d, e0 + e, c);
         } else {
           for (uint64_t k = e0 + e; k < d.n; ++k) {
             float x, y;
@@ -256,47 +265,51 @@ void cut_units(G& g) {
   g.grid = static_cast<uint32_t>(std::min(u, kMaxGrid));
 }
 
-// Whether a launch's inputs are loaded non-temporal.  Tuning override (read
-// once per process): GVM_STREAM_NT = 0 / 1.
+// How a launch loads its `operands` inputs of 4 bytes an element.  Tuning
+// override (read once per process): GVM_STREAM_NT = 0 (cached) / 1 (not).
 template <class G>
-bool stream_nt(const G& g, uint64_t bytes_per_element) {
+Loads stream_loads(const G& g, uint64_t operands) {
   static const int env = [] {
     const char* e = getenv("GVM_STREAM_NT");
     return e ? atoi(e) : -1;
   }();
-  if (env >= 0) return env != 0;
+  if (env >= 0) return env != 0 ? kNoneCached : kAllCached;
   uint64_t n = 0;
   for (uint32_t i = 0; i < g.count; ++i) n += g.d[i].n;
-  return n > kCachedInput / bytes_per_element;
+  return n <= kCachedInput / 4 / operands ? kAllCached : n <= kCachedInput / 4 ? kLastCached : kNoneCached;
 }
 
-template <class Op, int V4, bool NT>
+template <class Op, int V4, Loads LOADS>
 hipError_t launch_vec_shape(const VecGroup& g0, hipStream_t s) {
   if (g0.count == 1) {
     VecGroupN<1> g{1, 0, 0, {g0.d[0]}};
     cut_units<V4>(g);
-    return launch_group(vec_group_kernel<Op, V4, NT, 1>, g.grid, kThreads, s, g);
+    return launch_group(vec_group_kernel<Op, V4, LOADS, 1>, g.grid, kThreads, s, g);
   }
   VecGroup g = g0;
   cut_units<V4>(g);
-  return launch_group(vec_group_kernel<Op, V4, NT, kMaxGroup>, g.grid, kThreads, s, g);
+  return launch_group(vec_group_kernel<Op, V4, LOADS, kMaxGroup>, g.grid, kThreads, s, g);
 }
 
 template <class Op>
 hipError_t launch_vec(const VecGroup& g, hipStream_t s) {
-  return stream_nt(g, 8) ? launch_vec_shape<Op, 4, true>(g, s) : launch_vec_shape<Op, 2, false>(g, s);
+  switch (stream_loads(g, 2)) {
+    case kAllCached: return launch_vec_shape<Op, 2, kAllCached>(g, s);
+    case kLastCached: return launch_vec_shape<Op, 4, kLastCached>(g, s);
+    default: return launch_vec_shape<Op, 4, kNoneCached>(g, s);
+  }
 }
 
-template <int V4, bool NT, bool SAFE>
+template <int V4, Loads LOADS, bool SAFE>
 hipError_t launch_bs_shape(const BsGroup& g0, hipStream_t s) {
   if (g0.count == 1) {
     BsGroupN<1> g{1, 0, 0, g0.rate, g0.volatility, {g0.d[0]}};
     cut_units<V4>(g);
-    return launch_group(bs_group_kernel<V4, NT, SAFE, 1>, g.grid, kThreads, s, g);
+    return launch_group(bs_group_kernel<V4, LOADS, SAFE, 1>, g.grid, kThreads, s, g);
   }
   BsGroup g = g0;
   cut_units<V4>(g);
-  return launch_group(bs_group_kernel<V4, NT, SAFE, kMaxGroup>, g.grid, kThreads, s, g);
+  return launch_group(bs_group_kernel<V4, LOADS, SAFE, kMaxGroup>, g.grid, kThreads, s, g);
 }
 
 }  // namespace
@@ -309,8 +322,12 @@ hipError_t launch_bs_group(const BsGroup& g, hipStream_t s) {
   // 1 / sigma refines a quotient in this range; outside it (zero, NaN) the
   // kernel with the library's divide runs
   const float v = std::fabs(g.volatility);
-  if (!(v >= 0x1p-60f && v <= 0x1p60f)) return launch_bs_shape<2, false, true>(g, s);
-  return stream_nt(g, 12) ? launch_bs_shape<4, true, false>(g, s) : launch_bs_shape<2, false, false>(g, s);
+  if (!(v >= 0x1p-60f && v <= 0x1p60f)) return launch_bs_shape<2, kAllCached, true>(g, s);
+  switch (stream_loads(g, 3)) {
+    case kAllCached: return launch_bs_shape<2, kAllCached, false>(g, s);
+    case kLastCached: return launch_bs_shape<4, kLastCached, false>(g, s);
+    default: return launch_bs_shape<4, kNoneCached, false>(g, s);
+  }
 }
 
 }  // namespace gvm

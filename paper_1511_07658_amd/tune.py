@@ -6,10 +6,12 @@ identical-size requests (resident in HBM) through the GVM manager for every
 compiled tile configuration, times the launches with the manager's HIP
 events, and keeps the fastest configuration.  Each size starts with about
 60 ms of untimed launches (the engine clock climbs for about 20 ms under
-load), then passes over the configurations in index order and in reverse.  The result is written as the
-compiled-in table ``csrc/gemm_tiles.inc`` (rows of {largest n, config}),
-so the tile choice stays a pure function of n: a rank's SGEMM result does
-not depend on what it is grouped with.
+load), then passes over the configurations in index order and in reverse.
+The result is written as the compiled-in table ``csrc/gemm_tiles.inc`` (rows of
+{largest n, config}).  A launch of eight requests of one size takes its tiles
+from the table, any other launch from the cost formula of
+``csrc/gemm_choice.hpp``; every configuration gives a request the same bits, so
+its result does not depend on what it is grouped with.
 
     python -m paper_1511_07658_amd.tune [--sizes 256,512,...] [--group 8] [--reps 10] [--rounds 2] [--write] [--json out.json]
     python -m paper_1511_07658_amd.tune --from-json a.json,b.json    # table from saved sweeps (mean time)
