@@ -87,13 +87,13 @@ SGEMM_SOURCES = ("sgemm.hip", "group_device.hpp", "kernels.hpp", "gemm_tiles.inc
 STREAM_SOURCES = ("stream_kernels.hip", "group_device.hpp", "kernels.hpp")
 MEASURED_TRAFFIC = {
     "mixed32": {"sources": SGEMM_SOURCES, "kernels_sha256": "cad9c1fd38d1062206dfb19bc0ce900bf65e1d64a7e55ef74dc590413e4104ba",
-                "fetch_kib": 453902.0, "fetch_factor": 2.000, "write_kib": 85152.0, "write_factor": 1.000},
+                "fetch_kib": 453686.5, "fetch_factor": 2.000, "write_kib": 85152.0, "write_factor": 1.000},
     "sgemm8": {"sources": SGEMM_SOURCES, "kernels_sha256": "cad9c1fd38d1062206dfb19bc0ce900bf65e1d64a7e55ef74dc590413e4104ba",
                "fetch_kib": 32857.4, "fetch_factor": 2.000, "write_kib": 32768.0, "write_factor": 1.000},
-    "bs16": {"sources": STREAM_SOURCES, "kernels_sha256": "073ce6a597552763cc336c5dba9c28759575aced10567c93a84c9bd4e901bff1",
-             "fetch_kib": 393307.5, "fetch_factor": 2.000, "write_kib": 524288.9, "write_factor": 1.000},
-    "vecadd16": {"sources": STREAM_SOURCES, "kernels_sha256": "073ce6a597552763cc336c5dba9c28759575aced10567c93a84c9bd4e901bff1",
-                 "fetch_kib": 1048598.0, "fetch_factor": 2.000, "write_kib": 1048576.0, "write_factor": 1.000},
+    "bs16": {"sources": STREAM_SOURCES, "kernels_sha256": "3fd691942018381488f239707ce182aee27b3add4676f8f6153e862e3f262f8f",
+             "fetch_kib": 393299.0, "fetch_factor": 2.000, "write_kib": 524289.4, "write_factor": 1.000},
+    "vecadd16": {"sources": STREAM_SOURCES, "kernels_sha256": "3fd691942018381488f239707ce182aee27b3add4676f8f6153e862e3f262f8f",
+                 "fetch_kib": 1048596.5, "fetch_factor": 2.000, "write_kib": 1048576.1, "write_factor": 1.000},
 }
 
 

@@ -65,7 +65,7 @@ __device__ __forceinline__ f32x4 op4(Op op, f32x4 a, f32x4 b) {
 
 // Bound by memory.  The operands of a request of odd length start anywhere
 // (b is a + n), so every access is 16 bytes at float alignment: 14.5M elements
-// 27.6 us (6.3 TB/s, as 2^24 has), 34.8 element by element.
+// 26.0 us (6.7 TB/s, 2^24 has 6.9), 34.8 element by element.
 template <class Op, int V4, Loads LOADS, int N>
 __global__ __launch_bounds__(kThreads) void vec_group_kernel(VecGroupN<N> g) {
   constexpr uint64_t kUnit = V4 * 4 * kThreads;
