@@ -131,7 +131,7 @@ void CopyEngine::submit(void* dst, const void* src, size_t bytes, std::atomic<in
   // copies there is nothing to share, and small chunks cost throughput: 64
   // ranks at 1000 requests/s of 0.25-64 MiB saw p50 2.5 -> 28-66 ms and p99
   // 60 -> 800 ms when every copy was cut into eight.
-  const size_t eighth = std::min(kMaxChunk, std::max(kMinChunk, (bytes / 8 + 4095) & ~size_t(4095)));
+  const size_t eighth = std::min(kMaxChunk, std::max(kMinChunk, ((bytes + 7) / 8 + 4095) & ~size_t(4095)));
   size_t n;
   {
     std::lock_guard<std::mutex> lk(mu_);
