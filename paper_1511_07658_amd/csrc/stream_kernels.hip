@@ -142,7 +142,6 @@ __device__ __forceinline__ void norm_cdf_as(float x, float& n, float& m) {
 struct BsParams {
   float r, v, inv_v, half_v2;
 };
-__device__ __forceinline__ bool plain_range(float x) { return fabsf(x) >= 0x1p-100f && fabsf(x) <= 0x1p100f; }
 
 template <bool SAFE>
 __device__ __forceinline__ void bs_price(float S, float K, float T, const BsParams& c, float& call, float& put) {
@@ -167,12 +166,16 @@ __device__ __forceinline__ void bs_price(float S, float K, float T, const BsPara
   put = kd * m2 - S * m1;
 }
 
-// One option; an operand that a bare reciprocal does not serve (strikes of
-// extreme magnitude, infinities) is priced again with the library's divide,
-// whatever its neighbours are, so an option's bits depend on itself alone.
+// One option; operands that a bare reciprocal does not serve are priced again
+// with the library's divide, whatever their neighbours are, so an option's bits
+// depend on itself alone.  The step on the remainder turns a quotient beyond
+// the float range, or an infinite root, into NaN where a divide keeps it
+// infinite.  Between these bounds |S / K| stays below 2^120 and, with v within
+// 2^-60 .. 2^60 (the launch's rule), 1 / (v sqrt T) below 2^90; a NaN operand
+// passes the test and gives NaN either way.
 template <bool SAFE>
-__device__ __forceinline__ bool bs_extreme(float S, float K) {
-  return !SAFE && !(plain_range(K) && fabsf(S) <= 0x1p100f);
+__device__ __forceinline__ bool bs_extreme(float S, float K, float T) {
+  return !SAFE && (fmaxf(fabsf(S), fabsf(K)) > 0x1p60f || fminf(fabsf(K), T) < 0x1p-60f);
 }
 
 template <bool SAFE, int V4, Loads LOADS>
@@ -197,12 +200,12 @@ __device__ __forceinline__ void bs_quads(const BsDesc& d, uint64_t e, const BsPa
       bs_price<SAFE>(S[j][k], K[j][k], T[j][k], c, x, y);
       call[k] = x;
       put[k] = y;
-      extreme |= bs_extreme<SAFE>(S[j][k], K[j][k]);
+      extreme |= bs_extreme<SAFE>(S[j][k], K[j][k], T[j][k]);
     }
     if (__builtin_expect(extreme, 0)) {
 #pragma unroll
       for (int k = 0; k < 4; ++k)
-        if (bs_extreme<SAFE>(S[j][k], K[j][k])) {
+        if (bs_extreme<SAFE>(S[j][k], K[j][k], T[j][k])) {
           float x, y;
           bs_price<true>(S[j][k], K[j][k], T[j][k], c, x, y);
           call[k] = x;
@@ -235,7 +238,7 @@ __global__ __launch_bounds__(kThreads) void bs_group_kernel(BsGroupN<N> g) {
         } else {
           for (uint64_t k = e0 + e; k < d.n; ++k) {
             float x, y;
-            if (bs_extreme<SAFE>(d.S[k], d.K[k])) bs_price<true>(d.S[k], d.K[k], d.T[k], c, x, y);
+            if (bs_extreme<SAFE>(d.S[k], d.K[k], d.T[k])) bs_price<true>(d.S[k], d.K[k], d.T[k], c, x, y);
             else bs_price<SAFE>(d.S[k], d.K[k], d.T[k], c, x, y);
             d.call[k] = x;
             d.put[k] = y;
