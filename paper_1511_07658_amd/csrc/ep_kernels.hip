@@ -33,8 +33,8 @@ constexpr uint64_t kPhiloxW0 = 0x9E3779B97F4A7C15ull, kPhiloxW1 = 0xBB67AE8584CA
 
 // 128-bit product from four 32 x 32 + 64 bit multiply-adds.  The third one's
 // carry goes into the top word as a 0 / 1 register: the multiply-add gives it
-// in a scalar pair, which plain C++ recomputes with a compare (2^27 pairs 503 us,
-// 445 this way).  A vector instruction may read a scalar pair written by another
+// in a scalar pair, which plain C++ recomputes with a compare (13 % slower
+// at 2^27 pairs).  A vector instruction may read a scalar pair written by another
 // only after two wait states, and the compiler does not look into inline
 // assembly, so the write, the wait and the read are one block.
 __device__ __forceinline__ void mul128(uint64_t m, uint64_t a, uint64_t& hi, uint64_t& lo) {
@@ -101,11 +101,30 @@ __device__ __forceinline__ void philox_block(uint64_t b, uint64_t k0, uint64_t k
 // (2^15 pairs: 5.2 -> 4.8 us with the shorter sums below).
 constexpr int kLogTable = 256;
 constexpr double kLn2 = 0x1.62e42fefa39efp-1;
-struct LogEntry {
+struct alignas(16) LogEntry {
   double inv, m2log;
 };
 __device__ const LogEntry kLogEntries[kLogTable] = {
 #include "ep_log_table.inc"
+};
+__device__ const double kLogLow[kLogTable] = {   // what the rounded m2log lacks
+#include "ep_log_low.inc"
+};
+
+// The logarithms in two parts, to which e ln 2 (|e| <= 105) is added in two
+// parts: the upper ones are multiples of 2^-44, so their sum, below 2^8, is exact.
+__host__ __device__ constexpr double upper44(double x) { return (x + 0x1.8p8) - 0x1.8p8; }
+constexpr double kTwoLn2 = 2.0 * kLn2, kTwoLn2Low = 0x1.abc9e3b39803fp-55;
+constexpr double kTwoLn2Hi = upper44(kTwoLn2), kTwoLn2Lo = (kTwoLn2 - kTwoLn2Hi) + kTwoLn2Low;
+struct LogTable {
+  LogEntry e[kLogTable];   // {1/c, upper part}
+  double low[kLogTable];
+  __device__ __forceinline__ void fill(int i) {
+    const LogEntry x = kLogEntries[i];
+    const double hi = upper44(x.m2log);
+    e[i] = LogEntry{x.inv, hi};
+    low[i] = (x.m2log - hi) + kLogLow[i];
+  }
 };
 
 // A thread's annulus counts within one work unit, 8 bits each: counts 0..7
@@ -135,12 +154,17 @@ __device__ __forceinline__ double centred(uint64_t w) {
 // about one pair in 10^14).
 //
 // x, y and t are carried as 2^63 x, 2^63 y and 2^126 t (powers of two: every
-// rounding is the one of the definition).  The factor sqrt(-2 ln t / t) is
-// s / sqrt(s t) with s = -2 ln t: one reciprocal root and a third-order step
-// instead of a division and a root, and s from the table above, the exponent
-// and a polynomial of six terms (|r| <= 2^-9, or 2^-8 in the first interval:
-// the term left out is below 2^-57 of s).
-__device__ __forceinline__ int ep_pair(uint64_t wx, uint64_t wy, const LogEntry* table, double& sx, double& sy,
+// rounding is the one of the definition).  The factor is f = sqrt(s / t) with s =
+// -2 ln t, from the table above, the exponent and a polynomial (|r| <= 2^-9, or
+// 2^-8 in the first interval: the term left out is below 2^-57 of s).  With y0
+// near 1 / sqrt(s t), f0 = s y0 is near f, and s - f0^2 t, from the parts of s
+// before they are rounded to one, corrects it: one third-order step instead of a
+// division and a root, and two roundings that count (f0 t under the root, f).
+// Root mean square and largest error of f in 2^-53 over 2 x 10^7 pairs, emulated:
+// 0.468 and 1.86, against 0.520 and 1.89 of a correctly rounded logarithm, divide
+// and root (the product of a rounded s with the reciprocal root: 0.752 and 3.24,
+// and 445 -> 477 us for 2^27 pairs).
+__device__ __forceinline__ int ep_pair(uint64_t wx, uint64_t wy, const LogTable& table, double& sx, double& sy,
                                        Tally& q) {
 #pragma clang fp contract(off)
   const double x = centred(wx), y = centred(wy);
@@ -151,19 +175,22 @@ __device__ __forceinline__ int ep_pair(uint64_t wx, uint64_t wy, const LogEntry*
   const int e = static_cast<int>(th >> 20) - (1022 + 126);
   const double m = __longlong_as_double((static_cast<uint64_t>((th & 0xFFFFFu) | 0x3FE00000u) << 32) |
                                         static_cast<uint32_t>(tb));
-  const LogEntry c = table[(th >> 12) & (kLogTable - 1)];
+  const uint32_t i = (th >> 12) & (kLogTable - 1);
+  const LogEntry c = table.e[i];
   const double r = __builtin_fma(m, c.inv, -1.0);
   double p = __builtin_fma(r, 1.0 / 3.0, -2.0 / 5.0);
   p = __builtin_fma(r, p, 1.0 / 2.0);
   p = __builtin_fma(r, p, -2.0 / 3.0);
   p = __builtin_fma(r, p, 1.0);
-  p = __builtin_fma(r, p, -2.0);
-  const double s = __builtin_fma(r, p, __builtin_fma(static_cast<double>(e), -2.0 * kLn2, c.m2log));
-  const double st = fmax(s * t, 0x1p-900);  // t = 1: s = 0
-  const double y0 = __builtin_amdgcn_rsq(st);
-  const double d = __builtin_fma(-(st * y0), y0, 1.0);
-  const double y1 = __builtin_fma(y0 * d, __builtin_fma(d, 0.375, 0.5), y0);
-  const double f = ok ? s * y1 : 0.0;       // 2^-63 sqrt(-2 ln t / t)
+  const double ed = static_cast<double>(e);
+  const double hi = __builtin_fma(ed, -kTwoLn2Hi, c.m2log);   // s = hi - 2 r + lo
+  const double lo = __builtin_fma(r * r, p, __builtin_fma(ed, -kTwoLn2Lo, table.low[i]));
+  const double s = __builtin_fma(-2.0, r, hi) + lo;
+  const double y0 = __builtin_amdgcn_rsq(__builtin_fma(s, t, 0x1p-900));   // t = 1: s = 0
+  const double f0 = s * y0, u = f0 * t;
+  const double rest = __builtin_fma(-2.0, r, __builtin_fma(-u, f0, hi)) + lo;
+  const double d = __builtin_fma(-u, y0, 1.0);
+  const double f = ok ? __builtin_fma(rest * y0, __builtin_fma(d, 0.375, 0.5), f0) : 0.0;   // 2^-63 sqrt(-2 ln t / t)
   const double X = x * f, Y = y * f;
   sx += X;
   sy += Y;
@@ -217,7 +244,7 @@ static_assert(sizeof(EpRecord) == kEpRecordBytes, "record layout");
 // 256 threads left a request of 2^15 pairs to one CU: 88 us).
 template <int N>
 __global__ __launch_bounds__(kEpThreads) void ep_units_kernel(EpGroupN<N> g) {
-  __shared__ LogEntry table[kLogTable];
+  __shared__ LogTable table;
   __shared__ double wsx[kEpWaves], wsy[kEpWaves];
   __shared__ uint64_t wq[kEpWaves][3];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -230,7 +257,7 @@ __global__ __launch_bounds__(kEpThreads) void ep_units_kernel(EpGroupN<N> g) {
     const uint64_t k0 = d.inline_key ? d.key_value[0] : d.key[0];
     const uint64_t k1 = d.inline_key ? d.key_value[1] : d.key[1];
     if (d.inline_key && local == 0 && threadIdx.x < 2) d.key[threadIdx.x] = threadIdx.x ? k1 : k0;
-    if (u == blockIdx.x && threadIdx.x < kLogTable) table[threadIdx.x] = kLogEntries[threadIdx.x];
+    if (u == blockIdx.x && threadIdx.x < kLogTable) table.fill(threadIdx.x);
     uint64_t h, l;
     mul128(kPhiloxM0, k0, h, l);
     double sx = 0.0, sy = 0.0;
