@@ -10,6 +10,7 @@
 #include <time.h>
 #include <unistd.h>
 
+#include <algorithm>
 #include <climits>
 #include <cstdlib>
 #include <cstring>
@@ -94,6 +95,16 @@ int cu_partition_masks(uint32_t latency_cus, uint32_t* latency_mask, uint32_t* b
     (lat ? latency_mask : bulk_mask)[i / 32] |= 1u << (i % 32);
   }
   return GVM_OK;
+}
+
+int partition_carrying_cus(const uint32_t* mask) {
+  int engines = 0, fewest = kPartitionCus;
+  for (uint32_t b = 0; b < 4; ++b) {
+    int n = 0;
+    for (int w = 0; w < kPartitionCus / 32; ++w) n += __builtin_popcount(mask[w] & (0xFFu << (8 * b)));
+    if (n) ++engines, fewest = std::min(fewest, n);
+  }
+  return engines * fewest;
 }
 
 int futex_wait(std::atomic<uint32_t>* word, uint32_t expected, int64_t timeout_ns) {

@@ -40,10 +40,6 @@ uint64_t piece_bytes();
 void set_piece_bytes(uint64_t bytes);
 inline uint32_t piece_count(uint64_t bytes) { return static_cast<uint32_t>((bytes + piece_bytes() - 1) / piece_bytes()); }
 
-// A request whose copies total at most this many bytes keeps them on the
-// stream that runs its kernel: such a copy takes ~18 us on the link, less
-// than a dependency between two hardware queues costs (~15-20 us), and it
-// gains nothing from the copy FIFOs.
 // CU partition for serving QoS (gvm_config.latency_cus), on a device of
 // kPartitionCus CUs: bit i of a mask is CU i in HIP's numbering.  Write
 // i = 32a + 8b + c with c = i % 8, b = (i / 8) % 4 and a = i / 32.  The
@@ -57,7 +53,16 @@ inline uint32_t piece_count(uint64_t bytes) { return static_cast<uint32_t>((byte
 // GVM_EINVAL for other values of latency_cus.
 constexpr int kPartitionCus = 256;
 int cu_partition_masks(uint32_t latency_cus, uint32_t* latency_mask, uint32_t* bulk_mask);
+// CUs that carry a launch in a partition.  Workgroups are dealt evenly to the
+// shader engines (bits 3-4 of a CU's index, b above) that have a CU, so the one
+// with the fewest sets the rate: 224 CUs with one engine halved ran SGEMM 2048
+// at 70 TFLOP/s, as 128 would.
+int partition_carrying_cus(const uint32_t* mask);
 
+// A request whose copies total at most this many bytes keeps them on the
+// stream that runs its kernel: such a copy takes ~18 us on the link, less
+// than a dependency between two hardware queues costs (~15-20 us), and it
+// gains nothing from the copy FIFOs.
 constexpr uint64_t kLocalCopyBytes = 1ull << 20;
 
 // EP-like kernel: the 64-bit words of a request's output (sx, sy, q[0..9]),

@@ -178,11 +178,13 @@ class HipDevice final : public Device {
   // Pinned staging of a rank, allocated on first use.  Non-coherent
   // (coarse-grained) host memory: the device's copy engines move it to and
   // from HBM at the link's rate in both directions (57 GB/s device to host,
-  // against 30 GB/s for coherent memory, 97 GB/s both ways at once), and the
-  // staging is only ever touched by hipMemcpyAsync on the device side, whose
-  // completion the host observes through events with the default system-scope
-  // fence before it reads a result.  GVM_STAGING_COHERENT=1 takes coherent
-  // memory instead (measurement).
+  // against 30 GB/s for coherent memory, 97 GB/s both ways at once).  The device
+  // touches it by hipMemcpyAsync, and by the stores of the EP-like kernel
+  // (inline_io), which stay in the device's caches until a system-scope release.
+  // So the host reads a result only after an event with the default
+  // system-scope fence, recorded after the copy or the launch: a job's done
+  // event is a sync_event (or span1), never a launch_mark.
+  // GVM_STAGING_COHERENT=1 takes coherent memory instead (measurement).
   uint8_t* staging(int rank) override {
     if (rank < 0 || rank >= static_cast<int>(staging_.size())) return nullptr;
     if (!staging_[rank]) {
@@ -610,7 +612,9 @@ class HipDevice final : public Device {
   // no system-scope fence when it is reached (a fence writes back and
   // invalidates the caches, which added 10-14 us to a launch's measured
   // time on some devices).  Nothing waits on it or queries it; the stream
-  // order after a launch comes from ordinary events.
+  // order after a launch comes from ordinary events.  It must not become a
+  // job's done event: without the fence the host could read an old result
+  // where a kernel stored it to the staging.
   hipEvent_t launch_mark() {
     hipEvent_t e = nullptr;
     if (!free_marks_.empty()) {
@@ -707,18 +711,10 @@ class HipDevice final : public Device {
   }
 
   // CUs that carry an SGEMM launch of the masked partition a job runs in, 0
-  // outside one.  Workgroups are dealt evenly to the shader engines (bits 3-4
-  // of a CU's index) that have a CU, so the one with the fewest sets the rate:
-  // 224 CUs with one engine halved ran 2048^2 at 70 TFLOP/s, as 128 would.
+  // outside one.
   int part_cus(const Job* j) const {
     if (j->part < 0 || part_streams_.size() != 2 || !part_masked_) return 0;
-    int engines = 0, fewest = kPartitionCus;
-    for (uint32_t b = 0; b < 4; ++b) {
-      int n = 0;
-      for (uint32_t w : part_mask_[j->part]) n += __builtin_popcount(w & (0xFFu << (8 * b)));
-      if (n) ++engines, fewest = std::min(fewest, n);
-    }
-    return engines * fewest;
+    return partition_carrying_cus(part_mask_[j->part]);
   }
 
   // The plan's view of a job (one with inline_io has no copies, and completes
@@ -959,7 +955,7 @@ class HipDevice final : public Device {
           break;
         case kOpLaunch: {
           rc = launch_group(p.groups[static_cast<size_t>(o.group)], jobs, s, b, timed);
-          if (rc == GVM_OK && o.ev >= 0) {  // the end of the launch on its stream
+          if (rc == GVM_OK && o.ev >= 0) {  // the end of the launch on its stream; with the fence a done event needs
             hipEvent_t end = sync_event(b);
             if (!end) return GVM_EDEVICE;
             HIPCHK(hipEventRecord(end, s));
