@@ -35,7 +35,15 @@ from . import workloads as wl
 HERE = os.path.dirname(os.path.abspath(__file__))
 TABLE = os.path.join(HERE, "csrc", "gemm_tiles.inc")
 NUM_CONFIGS = 31
-CONFIG_NAMES = ['32x32x32R4m16P', '32x32x32R2m16P', '32x32x64R2m16P', '32x64x32R2m16P', '32x64x64R2m16P', '64x32x32R2m16P', '64x64x32R2m16w8P', '64x64x32R4m16P', '64x64x32R2P', '64x64x16R4P', '64x64x64R2P', '64x96x32R2m16P', '96x64x32R2m16P', '96x96x32R2m16P', '96x128x32R2m16P', '128x96x32R2m16P', '64x128x16R4P', '64x128x32R2P', '128x64x32R2w8P', '128x64x32R2P', '128x128x16R2P', '128x128x32R2P', '128x128x16R4w8P', '128x128x32R2w8P', '128x256x16R2w8P', '256x128x16R2w8P', '64x256x16R2P', '256x64x16R2P', '128x192x32R2m16w8', '192x128x32R2m16w8', '160x64x32R2m16P']
+# tile and k-step, "R": B row-major in LDS, k-tiles fetched ahead; "m16": the
+# 16x16x4 MFMA instead of 32x32x2; "w8": eight waves instead of four; "P": the
+# next k-tile's fragments read from LDS during the current MFMAs
+CONFIG_NAMES = ["32x32x32R4m16P", "32x32x32R2m16P", "32x32x64R2m16P", "32x64x32R2m16P", "32x64x64R2m16P",
+                "64x32x32R2m16P", "64x64x32R2m16w8P", "64x64x32R4m16P", "64x64x32R2P", "64x64x16R4P", "64x64x64R2P",
+                "64x96x32R2m16P", "96x64x32R2m16P", "96x96x32R2m16P", "96x128x32R2m16P", "128x96x32R2m16P",
+                "64x128x16R4P", "64x128x32R2P", "128x64x32R2w8P", "128x64x32R2P", "128x128x16R2P", "128x128x32R2P",
+                "128x128x16R4w8P", "128x128x32R2w8P", "128x256x16R2w8P", "256x128x16R2w8P", "64x256x16R2P",
+                "256x64x16R2P", "128x192x32R2m16w8", "192x128x32R2m16w8", "160x64x32R2m16P"]
 
 
 def warmup_launches(n, group, target_ms=60.0):
@@ -138,7 +146,12 @@ def tune(sizes, group=8, reps=10, configs=None, rounds=2):
 def merge_sweeps(sweeps):
     """One result per size from several saved sweeps: the mean time of each
     configuration over the sweeps that timed it, fastest mean first (ties to
-    0.1 us go to the lower configuration index)."""
+    0.1 us go to the lower configuration index).  A sweep that timed a
+    configuration this build does not have is one of other kernels, whose times
+    under the names still in use are not this build's either: ValueError."""
+    unknown = sorted({c for s in sweeps for r in s.values() for c in r["us"]} - set(CONFIG_NAMES))
+    if unknown:
+        raise ValueError(f"the sweep timed configurations that this build does not have: {', '.join(unknown)}")
     out = {}
     for n in sorted({int(k) for s in sweeps for k in s}):
         runs = [s[str(n)]["us"] for s in sweeps if str(n) in s]
