@@ -175,4 +175,15 @@ BatchPlan plan_grouped(const std::vector<PlanJob>& jobs, bool graph, int compute
   return p;
 }
 
+bool span_on_fifos(int policy, const std::vector<PlanJob>& jobs) {
+  if (policy != GVM_POLICY_PS1 && policy != GVM_POLICY_PS2) return false;
+  size_t in = 0, out = 0;
+  for (const PlanJob& j : jobs) {
+    if (j.pieces) return false;
+    in += j.copy_in && (!j.local || policy == GVM_POLICY_PS1);
+    out += j.copy_out && (!j.local || policy == GVM_POLICY_PS1);
+  }
+  return policy == GVM_POLICY_PS1 ? in && out : in == jobs.size() && out == jobs.size();
+}
+
 }  // namespace gvm

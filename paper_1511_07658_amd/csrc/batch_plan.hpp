@@ -91,4 +91,12 @@ std::vector<PlanGroup> plan_groups(const std::vector<PlanJob>& jobs, int nstream
 BatchPlan plan_grouped(const std::vector<PlanJob>& jobs, bool graph, int compute_streams = 2,
                        bool longest_first = true);
 
+// Timed span of a batch under PS-1 or PS-2: whether it can be recorded on the
+// copy FIFOs themselves, its start on H2D and its end on D2H.  That holds where
+// every kernel follows a whole copy-in of the batch and is followed by a copy-out
+// of it: under PS-1 (all copies on the FIFOs, the phases wait for each other) a
+// copy in each direction, under PS-2 both copies of every job on the FIFOs.  Input
+// pieces are queued before the batch, and a mark on H2D would come after them.
+bool span_on_fifos(int policy, const std::vector<PlanJob>& jobs);
+
 }  // namespace gvm

@@ -292,16 +292,16 @@ class HipDevice final : public Device {
       // only the streams that carry work of this batch (each extra stream
       // costs a cross-queue wait at both ends of the span)
       const bool per_rank = policy == GVM_POLICY_PS1 || policy == GVM_POLICY_PS2;
-      size_t in = 0, out = 0;   // jobs with a copy on the FIFOs
+      bool any_in = false, any_out = false;
+      std::vector<PlanJob> pj;
       for (Job* j : jobs) {
-        in += j->copy_in && (!j->local || policy == GVM_POLICY_PS1);
-        out += j->copy_out && (!j->local || policy == GVM_POLICY_PS1);
+        any_in |= j->copy_in && (!j->local || policy == GVM_POLICY_PS1);
+        any_out |= j->copy_out && (!j->local || policy == GVM_POLICY_PS1);
+        pj.push_back(plan_job(j));
       }
-      const bool any_in = in > 0, any_out = out > 0;
-      if (policy == GVM_POLICY_PS1 ? any_in && any_out : per_rank && in == jobs.size() && out == jobs.size()) {
-        // every kernel follows a copy-in, and every kernel is followed by a
-        // copy-out: the span needs no wait of its own (two queue hops, 20 us of
-        // a small request's 84 under PS-1, and of 1003 for a vector add of 2^22)
+      if (span_on_fifos(policy, pj)) {
+        // the span needs no wait of its own (two queue hops, 20 us of a small
+        // request's 84 under PS-1, and of 1003 for a vector add of 2^22)
         first = h2d_;
         last = d2h_;
       } else {
