@@ -132,9 +132,6 @@ struct LogTable {
 // pairs of a unit, so no field overflows).
 struct Tally {
   uint64_t lo = 0, hi = 0;
-  __device__ __forceinline__ uint32_t get(int l) const {
-    return static_cast<uint32_t>(((l < 8 ? lo : hi) >> (8 * (l & 7))) & 0xFF);
-  }
 };
 
 // 2^63 (2u - 1) with u = (w >> 11) 2^-53, exactly: the word's upper 53 bits
