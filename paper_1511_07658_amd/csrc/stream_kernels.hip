@@ -172,10 +172,11 @@ __device__ __forceinline__ void bs_price(float S, float K, float T, const BsPara
 // the float range, or an infinite root, into NaN where a divide keeps it
 // infinite.  Between these bounds |S / K| stays below 2^120 and, with v within
 // 2^-60 .. 2^60 (the launch's rule), 1 / (v sqrt T) below 2^90; a NaN operand
-// passes the test and gives NaN either way.
+// gives NaN either way.
 template <bool SAFE>
 __device__ __forceinline__ bool bs_extreme(float S, float K, float T) {
-  return !SAFE && (fmaxf(fabsf(S), fabsf(K)) > 0x1p60f || fminf(fabsf(K), T) < 0x1p-60f);
+  const float k = fabsf(K);
+  return !SAFE && (fabsf(S) > 0x1p60f || __builtin_amdgcn_fmed3f(k, 0x1p-60f, 0x1p60f) != k || T < 0x1p-60f);
 }
 
 template <bool SAFE, int V4, Loads LOADS>
@@ -217,9 +218,9 @@ __device__ __forceinline__ void bs_quads(const BsDesc& d, uint64_t e, const BsPa
   }
 }
 
-// Bound by memory at millions of options: 84 MB of 4M in 13.9-14.4 us, 13.6 at
+// Bound by memory at millions of options: 84 MB of 4M in 14.7-14.9 us, 13.6 at
 // the 6.17 TB/s of its access mix.  17.6 us with 102 instructions per option
-// (75 now); 300001 options 8.3 us element by element in 74 units of 4096, now
+// (76 now); 300001 options 8.3 us element by element in 74 units of 4096, now
 // 3.8 in units of 2048.
 template <int V4, Loads LOADS, bool SAFE, int N>
 __global__ __launch_bounds__(kThreads) void bs_group_kernel(BsGroupN<N> g) {
