@@ -70,11 +70,11 @@ MAX_GPU_PROCESSES = 16
 EP_FP64_OPS_PER_PAIR = 9.0 + math.pi / 4.0 * 9.0
 # VALU issue utilisation of the compiled kernel (a diagnostic of the code,
 # not a roofline): per Philox block (2 pairs per lane, both accepted) the unit
-# loop of csrc/ep_kernels.hip issues 271 wave64 VALU instructions: 171 of 4
-# cycles (binary64, 64-bit integer, 32-bit multiplies and compares), 98 plain
-# 32-bit ones of 2 and 2 binary64 roots of 16, the costs measured with loops of
-# one kind at two and more waves per SIMD.
-EP_SIMD_CYCLES_PER_PAIR = (171 * 4.0 + 98 * 2.0 + 2 * 16.0) / 128
+# loop of csrc/ep_kernels.hip issues 285 wave64 VALU instructions: 182 of 4
+# cycles (binary64, 64-bit integer, 32-bit multiplies, compares and selects),
+# 101 plain 32-bit ones of 2 and 2 binary64 roots of 16, the costs measured with
+# loops of one kind at two and more waves per SIMD.
+EP_SIMD_CYCLES_PER_PAIR = (182 * 4.0 + 101 * 2.0 + 2 * 16.0) / 128
 EP_ISSUE_GPAIRS = 256 * 4 * 2.4e9 / EP_SIMD_CYCLES_PER_PAIR / 1e9
 
 # HBM bytes per launch of the dominant kernel from rocprofv3 --pmc FETCH_SIZE /
@@ -86,14 +86,14 @@ SGEMM_SOURCES = ("sgemm.hip", "group_device.hpp", "kernels.hpp", "gemm_tiles.inc
                  "gemm_balance.hpp")
 STREAM_SOURCES = ("stream_kernels.hip", "group_device.hpp", "kernels.hpp")
 MEASURED_TRAFFIC = {
-    "mixed32": {"sources": SGEMM_SOURCES, "kernels_sha256": "cad9c1fd38d1062206dfb19bc0ce900bf65e1d64a7e55ef74dc590413e4104ba",
-                "fetch_kib": 453686.5, "fetch_factor": 2.000, "write_kib": 85152.0, "write_factor": 1.000},
-    "sgemm8": {"sources": SGEMM_SOURCES, "kernels_sha256": "cad9c1fd38d1062206dfb19bc0ce900bf65e1d64a7e55ef74dc590413e4104ba",
+    "mixed32": {"sources": SGEMM_SOURCES, "kernels_sha256": "3901cf6c2874550d65ef2cfe179359a58a952ba9422833e443345d812276c66a",
+                "fetch_kib": 453413.5, "fetch_factor": 2.000, "write_kib": 85152.0, "write_factor": 1.000},
+    "sgemm8": {"sources": SGEMM_SOURCES, "kernels_sha256": "3901cf6c2874550d65ef2cfe179359a58a952ba9422833e443345d812276c66a",
                "fetch_kib": 32857.4, "fetch_factor": 2.000, "write_kib": 32768.0, "write_factor": 1.000},
-    "bs16": {"sources": STREAM_SOURCES, "kernels_sha256": "3fd691942018381488f239707ce182aee27b3add4676f8f6153e862e3f262f8f",
-             "fetch_kib": 393299.0, "fetch_factor": 2.000, "write_kib": 524289.4, "write_factor": 1.000},
-    "vecadd16": {"sources": STREAM_SOURCES, "kernels_sha256": "3fd691942018381488f239707ce182aee27b3add4676f8f6153e862e3f262f8f",
-                 "fetch_kib": 1048596.5, "fetch_factor": 2.000, "write_kib": 1048576.1, "write_factor": 1.000},
+    "bs16": {"sources": STREAM_SOURCES, "kernels_sha256": "a18fbc7f651ba1e4198e0297dd4257522bb5f1b84072a3fa23c7f4fd7936da92",
+             "fetch_kib": 393310.0, "fetch_factor": 2.000, "write_kib": 524288.6, "write_factor": 1.000},
+    "vecadd16": {"sources": STREAM_SOURCES, "kernels_sha256": "a18fbc7f651ba1e4198e0297dd4257522bb5f1b84072a3fa23c7f4fd7936da92",
+                 "fetch_kib": 1048596.5, "fetch_factor": 2.000, "write_kib": 1048576.0, "write_factor": 1.000},
 }
 
 

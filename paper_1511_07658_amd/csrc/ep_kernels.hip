@@ -235,8 +235,9 @@ static_assert(sizeof(EpRecord) == kEpRecordBytes, "record layout");
 // Bound by VALU issue: with two waves or more on a SIMD a wave64 instruction
 // takes 4 cycles in binary64, in 64-bit integers and for 32-bit multiplies, a
 // plain 32-bit one 2 and a binary64 root 16 (measured with loops of one kind).
-// The 271 of two pairs come to about 910 cycles that way; a request of 2^27
-// pairs runs at 307 Gpairs/s, 1024 cycles at 2.4 GHz.  8 waves per workgroup on
+// The 285 of two pairs come to about 960 cycles that way; a request of 2^27
+// pairs runs at 281 Gpairs/s, 1120 cycles at 2.4 GHz (307 and 1024 with 14
+// instructions fewer and the larger error, see ep_pair).  8 waves per workgroup on
 // small units fill the SIMDs for requests of any size (a unit of 2^15 pairs on
 // 256 threads left a request of 2^15 pairs to one CU: 88 us).
 template <int N>

@@ -116,7 +116,7 @@ __device__ __forceinline__ f32x4 inside4(f32x4 x, int n, int r, int c) {
 // masked, once per tile.  Fetches are 16 bytes at any float alignment (a row
 // of n floats starts anywhere when n is odd).  n = 517: 73.7 us with masked
 // 4-byte fetches in 45 tiles of 64x128 (40 + 5 in a grid of whole rounds over
-// the XCDs), 7.2 us now.
+// the XCDs), 7.4 us now.
 //
 // Tiles in units, requests in order, tiles of a request row-major.  Workgroup
 // w runs on XCD w % 8, so unit (w % 8) * (grid / 8) + w / 8 gives each XCD a
@@ -496,8 +496,12 @@ int gemm_config_forced() {
 // The tuner times launches of kTableCount requests of one size, so its rows
 // hold for those; any other launch takes the cheapest configuration by the
 // cost formula, which knows how many tiles the launch has for the chip (one
-// 1024 x 1024 request: 18.5 us with the formula's 64x64 tiles, 119 us with the
-// 256x128 tiles that are within 1 % of the best for eight of them).
+// 1024 x 1024 request: 18.7 us with the formula's 64x64 tiles, 119 us with the
+// 256x128 tiles that are within 1 % of the best for eight of them).  For eight
+// requests, over the 32 multiples of 64 up to 2048, the two name the same tiles
+// at 19; at the others the table's are faster at small sizes (448: 20.8 and 22.8
+// us, 512: 23.7 and 24.4), the formula's at 384 (16.7 and 15.8) and by 1-2 % at
+// 768, 1152, 1280 and 1536, and 0.2 % lies between them on average.
 int gemm_config_for(uint32_t count, const uint32_t* n, int cus) {
   const int forced = gemm_config_forced();
   if (forced >= 0) return forced;
